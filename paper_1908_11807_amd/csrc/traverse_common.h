@@ -101,12 +101,18 @@ constexpr bool exact_leaf_slots() {
   return FMT == ABX_NODES_FP32 || KIND == ABX_PRIM_POINTS;
 }
 
+// The node's loads are kept together, ahead of everything that uses them: the
+// lanes of a wavefront read 64 different lines, far more wavefronts run than
+// a CU's L1 holds lines for, and a load scheduled behind arithmetic finds the
+// line that its predecessor fetched evicted (k = 10 on the C3 shell, one-lane
+// pass 133 ms with the loads left to the scheduler, 119 ms together).
 template <int KIND, int FMT>
 __device__ __forceinline__ void load_kids(const TreeArgs &t, int32_t node, Kids &k) {
   if (FMT == ABX_NODES_FP32) {
     const float4 *p = reinterpret_cast<const float4 *>(t.nodes) + 4 * (int64_t)node;
     const float4 a = p[0], b = p[1], c = p[2];
-    const int4 d = reinterpret_cast<const int4 *>(p)[3];
+    const int2 d = *reinterpret_cast<const int2 *>(p + 3);
+    __builtin_amdgcn_sched_barrier(0);
     k.l[0] = a.x; k.l[1] = a.y; k.l[2] = a.z; k.l[3] = a.w; k.l[4] = b.x; k.l[5] = b.y;
     k.r[0] = b.z; k.r[1] = b.w; k.r[2] = c.x; k.r[3] = c.y; k.r[4] = c.z; k.r[5] = c.w;
     k.lref = d.x;
@@ -114,6 +120,7 @@ __device__ __forceinline__ void load_kids(const TreeArgs &t, int32_t node, Kids 
   } else {
     const uint4 *p = reinterpret_cast<const uint4 *>(t.nodes) + 2 * (int64_t)node;
     const uint4 a = p[0], b = p[1];
+    __builtin_amdgcn_sched_barrier(0);
     const uint32_t w[6] = {a.x, a.y, a.z, a.w, b.x, b.y};
     k.lref = (int32_t)b.z;
     k.rref = (int32_t)b.w;
@@ -267,9 +274,28 @@ __device__ __forceinline__ float key_dist(int64_t key) {
 }
 __device__ __forceinline__ int32_t key_index(int64_t key) { return (int32_t)(uint32_t)key; }
 
-constexpr int64_t kKeySentinel = -1;  // precedes every candidate
+// precedes every candidate (as a double: -inf)
+constexpr int64_t kKeySentinel = (int64_t)0xfff0000000000000ull;
 // an empty slot: (+inf, INT_MAX), preceded by every finite candidate
 constexpr int64_t kKeyEmpty = (int64_t)(((uint64_t)0x7f800000u << 32) | 0x7fffffffu);
+
+// Smaller and larger of two keys.  Read as doubles, keys order like the
+// integers: candidates and the empty slot are finite and not negative (their
+// top bits are those of a float up to +inf, whose pattern is below a double's
+// exponent of infinity), denormal ones included, which the double-precision
+// minimum and maximum keep.  One instruction each, where the integer form
+// takes a compare and two selects.  (asm: the compiler would first
+// canonicalise both operands, an instruction each.)
+__device__ __forceinline__ int64_t key_min(int64_t a, int64_t b) {
+  int64_t r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ int64_t key_max(int64_t a, int64_t b) {
+  int64_t r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 
 // The k best candidates of one lane, ascending keys.  Slots [0, K-k) hold
 // sentinels that precede everything and never move; the k live slots start
@@ -282,23 +308,20 @@ struct KnnList {
     for (int j = 0; j < K; ++j) key[j] = j < K - k ? kKeySentinel : kKeyEmpty;
   }
   __device__ __forceinline__ float kth() const { return key_dist(key[K - 1]); }
-  // Insert x if it precedes the last entry, dropping the last entry.  With
-  // c_j = (x < key[j]) (false up to the insertion point, true after it), slot
-  // j keeps its entry, takes x, or takes its predecessor's entry.  Fully
-  // unrolled: constant register indices only.
+  // Insert x if it precedes the last entry, dropping the last entry: slot j
+  // becomes the median of x, its entry and its predecessor's entry.  Fully
+  // unrolled from the back (constant register indices, no copies): 2K - 1
+  // instructions, no chain between the slots.  Cheap enough for a wavefront
+  // to run at once for one lane: holding candidates back until several lanes
+  // had one, which paid while an insertion took ~7K instructions, was slower
+  // (k = 16 forest walk 13.6 ms with that, 11.6 with this insertion behind
+  // it, 11.2 inserting at once; k = 32 on the 1e7 shell, 1e5 queries,
+  // one-lane pass 8.2 -> 5.7 ms; k = 10 on 1e6 cube points 0.78 -> 0.69).
   __device__ __forceinline__ void offer_key(int64_t x) {
     if (x < key[K - 1]) {
-      bool c_prev = x < key[0];
-      int64_t prev = key[0];
-      if (c_prev) key[0] = x;
 #pragma unroll
-      for (int j = 1; j < K; ++j) {
-        const bool c = x < key[j];
-        const int64_t cur = key[j];
-        key[j] = c ? (c_prev ? prev : x) : cur;
-        prev = cur;
-        c_prev = c;
-      }
+      for (int j = K - 1; j > 0; --j) key[j] = key_max(key[j - 1], key_min(key[j], x));
+      key[0] = key_min(key[0], x);
     }
   }
   __device__ __forceinline__ void offer(float d, int32_t idx) { offer_key(knn_key(d, idx)); }
@@ -307,49 +330,6 @@ struct KnnList {
 #pragma unroll
     for (int j = 0; j + 1 < K; ++j) key[j] = key[j + 1];
     key[K - 1] = kKeyEmpty;
-  }
-};
-
-// Candidates waiting to enter a lane's list.  Inserting one costs ~70 VALU
-// operations for k = 10, and a wavefront pays them whenever any of its lanes
-// inserts; a lane meets a qualifying leaf in a few percent of its steps, so
-// nearly every step paid for one lane.  Lanes therefore park up to two
-// candidates and the wavefront inserts them together once kDeferLanes lanes
-// have one waiting (a third candidate goes in at once).  Pruning meanwhile
-// uses the list's k-th distance without the parked candidates: an upper
-// bound of the final one, so nothing the exact walk needs is pruned.
-constexpr int kDeferLanes = 4;
-
-// An empty parking slot.  Parked keys are never negative (a parked distance
-// passed a <= test, so it is a non-negative number, and indices are
-// non-negative), so -1 marks an empty slot; as an inline constant it costs
-// one move to set, where a wider constant can end up reloaded from private
-// memory inside the walk loop.
-constexpr int64_t kPendNone = -1;
-
-struct KnnPending {
-  int64_t a, b;
-  __device__ __forceinline__ void init() { a = b = kPendNone; }
-  template <int K>
-  __device__ __forceinline__ void park(KnnList<K> &L, int64_t x) {
-    if (a == kPendNone) a = x;
-    else if (b == kPendNone) b = x;
-    else L.offer_key(x);
-  }
-  // called by every active lane of the wavefront
-  template <int K>
-  __device__ __forceinline__ void flush_some(KnnList<K> &L) {
-    if (__popcll(__ballot(a != kPendNone)) >= kDeferLanes && a != kPendNone) {
-      L.offer_key(a);
-      a = b;
-      b = kPendNone;
-    }
-  }
-  template <int K>
-  __device__ __forceinline__ void flush_all(KnnList<K> &L) {
-    if (a != kPendNone) L.offer_key(a);
-    if (b != kPendNone) L.offer_key(b);
-    a = b = kPendNone;
   }
 };
 
@@ -379,31 +359,32 @@ __device__ __forceinline__ void knn_leaf(const TreeArgs &t, const KnnQuery &q, i
 // One step of the nearest walk: visit `node`, offer its leaf children, and
 // return the nearer qualifying internal child (the farther one is pushed),
 // or -1 when neither qualifies.  `bound` is an external upper bound of the
-// final k-th distance (+inf when there is none).
-template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, bool DEFER = false, typename DT>
+// final k-th distance, used if BOUNDED.
+template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, bool BOUNDED = true, typename DT>
 __device__ __forceinline__ int32_t knn_visit2(const TreeArgs &t, const KnnQuery &q, int32_t node,
                                               float bound, KnnList<K> &L, ABX_LDS int32_t *lds_n,
                                               ABX_LDS DT *lds_d, int32_t *ovf_n, DT *ovf_d,
-                                              int &sp, int &nl, int32_t &reads,
-                                              KnnPending *pend = nullptr) {
+                                              int &sp, int &nl, int32_t &reads) {
+  auto limit = [&]() { return BOUNDED ? fminf(L.kth(), bound) : L.kth(); };
   Kids c;
   load_kids<KIND, FMT>(t, node, c);
   const float dl = box_dist2(c.l[0], c.l[1], c.l[2], c.l[3], c.l[4], c.l[5], q.x, q.y, q.z);
   const float dr = box_dist2(c.r[0], c.r[1], c.r[2], c.r[3], c.r[4], c.r[5], q.x, q.y, q.z);
   const bool ll = c.lref < 0, lr = c.rref < 0;
-  if (DEFER && exact_leaf_slots<KIND, FMT>()) {
-    const float thr0 = fminf(L.kth(), bound);
+  if (exact_leaf_slots<KIND, FMT>()) {
+    // both leaves tested against the bound before either enters the list: one
+    // insertion's code runs for whichever child offers
+    const float thr0 = limit();
     const bool ol = ll && dl <= thr0, orr = lr && dr <= thr0;
     if (ol || orr) {
-      pend->park(L, ol ? knn_key(dl, ~c.lref) : knn_key(dr, ~c.rref));
-      if (ol && orr) pend->park(L, knn_key(dr, ~c.rref));
+      L.offer_key(ol ? knn_key(dl, ~c.lref) : knn_key(dr, ~c.rref));
+      if (ol && orr) L.offer_key(knn_key(dr, ~c.rref));
     }
-    pend->flush_some(L);
   } else {
-    if (ll) knn_leaf<KIND, FMT, K>(t, q, ~c.lref, dl, fminf(L.kth(), bound), L, reads);
-    if (lr) knn_leaf<KIND, FMT, K>(t, q, ~c.rref, dr, fminf(L.kth(), bound), L, reads);
+    if (ll) knn_leaf<KIND, FMT, K>(t, q, ~c.lref, dl, limit(), L, reads);
+    if (lr) knn_leaf<KIND, FMT, K>(t, q, ~c.rref, dr, limit(), L, reads);
   }
-  const float thr = fminf(L.kth(), bound);
+  const float thr = limit();
   const bool gl = !ll && dl <= thr, gr = !lr && dr <= thr;
   if (gl && gr) {
     // Visit order only (pruning uses the box distances): the child whose box
@@ -476,30 +457,29 @@ __device__ __forceinline__ void wide_slots(const TreeArgs &t, int32_t node, cons
 // the qualifying internal children are visited nearest box centre first:
 // the nearest is returned and the others are pushed farthest first, so they
 // come off the stack in the same order.
-template <int KIND, int K, int B, int S = kLdsDepthNearest, bool DEFER = false, typename DT>
+template <int KIND, int K, int B, int S = kLdsDepthNearest, bool BOUNDED = true, typename DT>
 __device__ __forceinline__ int32_t knn_visit_w(const TreeArgs &t, const KnnQuery &q, int32_t node,
                                                float bound, KnnList<K> &L, ABX_LDS int32_t *lds_n,
                                                ABX_LDS DT *lds_d, int32_t *ovf_n, DT *ovf_d,
-                                               int &sp, int &nl, int32_t &reads,
-                                               KnnPending *pend = nullptr) {
+                                               int &sp, int &nl, int32_t &reads) {
   // each slot is decoded straight into its box distance and centre key, so
   // the 24 coordinates are never live together (they made the walk spill)
+  auto limit = [&]() { return BOUNDED ? fminf(L.kth(), bound) : L.kth(); };
   float d[4], key[4];
   int32_t r[4];
   wide_slots<KIND>(t, node, q, d, key, r);
-  if (DEFER && exact_leaf_slots<KIND, ABX_NODES_Q16W>()) {
-    const float thr0 = fminf(L.kth(), bound);
+  if (exact_leaf_slots<KIND, ABX_NODES_Q16W>()) {
+    const float thr0 = limit();
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (r[j] < 0 && r[j] != kEmptyRef && d[j] <= thr0) pend->park(L, knn_key(d[j], ~r[j]));
-    pend->flush_some(L);
+      if (r[j] < 0 && r[j] != kEmptyRef && d[j] <= thr0) L.offer_key(knn_key(d[j], ~r[j]));
   } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (r[j] < 0 && r[j] != kEmptyRef)
-        knn_leaf<KIND, ABX_NODES_Q16W, K>(t, q, ~r[j], d[j], fminf(L.kth(), bound), L, reads);
+        knn_leaf<KIND, ABX_NODES_Q16W, K>(t, q, ~r[j], d[j], limit(), L, reads);
   }
-  const float thr = fminf(L.kth(), bound);
+  const float thr = limit();
   // the qualifying internal children keep their key; the others sort last
   // with reference -1
 #pragma unroll
@@ -534,18 +514,17 @@ __device__ __forceinline__ int32_t knn_visit_w(const TreeArgs &t, const KnnQuery
   return r[0];
 }
 
-template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, bool DEFER = false, typename DT>
+template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, bool BOUNDED = true, typename DT>
 __device__ __forceinline__ int32_t knn_visit(const TreeArgs &t, const KnnQuery &q, int32_t node,
                                              float bound, KnnList<K> &L, ABX_LDS int32_t *lds_n,
                                              ABX_LDS DT *lds_d, int32_t *ovf_n, DT *ovf_d,
-                                             int &sp, int &nl, int32_t &reads,
-                                             KnnPending *pend = nullptr) {
+                                             int &sp, int &nl, int32_t &reads) {
   if constexpr (FMT == ABX_NODES_Q16W)
-    return knn_visit_w<KIND, K, B, S, DEFER>(t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d, sp,
-                                             nl, reads, pend);
+    return knn_visit_w<KIND, K, B, S, BOUNDED>(t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d, sp,
+                                               nl, reads);
   else
-    return knn_visit2<KIND, FMT, K, B, S, DEFER>(t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d,
-                                                 sp, nl, reads, pend);
+    return knn_visit2<KIND, FMT, K, B, S, BOUNDED>(t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d,
+                                                   sp, nl, reads);
 }
 
 // pop deferred nodes until one still qualifies; -1 when the stack runs dry
@@ -636,20 +615,17 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
     int sp = 0, nl = 0;
     int32_t node = info.root;
     const int64_t limit = budget < t.n ? budget : t.n;
-    KnnPending pend;
-    pend.init();
     done = false;
     for (int64_t it = 0; it < limit; ++it) {
       if (STATS) ++visited;
-      node = knn_visit<KIND, FMT, K, B, kWin, true>(
-          t, q, node, INFINITY, L, lds_n, lds_d, ovf_n, ovf_d, sp, nl, reads, &pend);
+      node = knn_visit<KIND, FMT, K, B, kWin, false>(t, q, node, INFINITY, L, lds_n, lds_d, ovf_n,
+                                                     ovf_d, sp, nl, reads);
       if (node < 0) node = knn_pop<B, kWin>(L.kth(), lds_n, lds_d, ovf_n, ovf_d, sp, nl);
       if (node < 0) {
         done = true;
         break;
       }
     }
-    pend.flush_all(L);
     if (!STATS && !done) {
       const uint32_t h = atomicAdd(heavy.count, 1u);
       heavy.q[h] = (int32_t)qi;
@@ -904,8 +880,6 @@ __global__ __launch_bounds__(CoopShape<W>::kThreads) void k_nearest_coop(
     bool active = true;
     int32_t node = -1;
     float bound = __uint_as_float(s_bound);
-    KnnPending pend;
-    pend.init();
     for (int64_t it = 0; it < 4 * t.n + 64; ++it) {
       // share the workgroup's bound (each lane also prunes with its own list)
       if ((it & ((1 << kCoopShareLog2) - 1)) == 0) {
@@ -921,13 +895,11 @@ __global__ __launch_bounds__(CoopShape<W>::kThreads) void k_nearest_coop(
         if (node < 0) {
           active = false;
         } else {
-          node = knn_visit<KIND, FMT, K, S::kThreads, S::kWindow, true>(
-              t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d, sp, nl, reads, &pend);
+          node = knn_visit<KIND, FMT, K, S::kThreads, S::kWindow>(t, q, node, bound, L, lds_n, lds_d,
+                                                                  ovf_n, ovf_d, sp, nl, reads);
         }
       }
     }
-
-    pend.flush_all(L);
 
     // merge: each wave takes the k best of its 64 lists (k rounds of a
     // wave-wide minimum over the list fronts), then wave 0 the k best of the
