@@ -150,9 +150,16 @@ __global__ __launch_bounds__(kTravBlock) void k_spatial(TreeArgs t, QueryArgs qa
 }
 
 // ------------------------------------------------------------------ nearest
+// One wavefront per workgroup: a walk's length varies, and a workgroup of four
+// held its LDS until its longest walk ended; a small batch also spreads over
+// four times as many CUs (1000 queries, k = 8, on 1e7 points: 209 -> 177 us a
+// call; 1e6 queries on 1e6 points 801 -> 776; workgroups of eight and twelve
+// wavefronts 10 % slower than four on the 1e7 shell).
+constexpr int kNearestBlock = kWave;
+
 // Pass 1 over one tree: one lane per query, queries in Morton order.
 template <int KIND, int FMT, int K, bool STATS>
-__global__ __launch_bounds__(kTravBlock)
+__global__ __launch_bounds__(kNearestBlock)
 __attribute__((amdgpu_waves_per_eu(nearest_waves_per_eu(K, FMT)))) void k_nearest(TreeArgs t, PlainMap map,
                                                         const float *__restrict__ pts, int64_t m,
                                                         const int32_t *__restrict__ order,
@@ -161,12 +168,12 @@ __attribute__((amdgpu_waves_per_eu(nearest_waves_per_eu(K, FMT)))) void k_neares
                                                         int32_t *__restrict__ stats, int64_t budget,
                                                         HeavyList heavy) {
   constexpr int W = lane_window(nearest_waves_per_eu(K, FMT));
-  __shared__ int32_t s_node[W * kTravBlock];
-  __shared__ uint16_t s_dist[W * kTravBlock];
-  const int64_t tq = xcd_tile(blockIdx.x, gridDim.x) * kTravBlock + threadIdx.x;
+  __shared__ int32_t s_node[W * kNearestBlock];
+  __shared__ uint16_t s_dist[W * kNearestBlock];
+  const int64_t tq = xcd_tile(blockIdx.x, gridDim.x) * kNearestBlock + threadIdx.x;
   if (tq >= m) return;
   const int64_t qi = order ? order[tq] : tq;
-  nearest_lane<KIND, FMT, K, STATS, kTravBlock, W>(
+  nearest_lane<KIND, FMT, K, STATS, kNearestBlock, W>(
       t, map, pts, qi, (ABX_LDS int32_t *)(s_node) + threadIdx.x,
       (ABX_LDS uint16_t *)(s_dist) + threadIdx.x, indices, dist, stats, budget, heavy);
 }
@@ -577,15 +584,15 @@ abx_status nearest_k(const abx_bvh *b, const float *pts, int64_t m, const int32_
   const TreeArgs t = tree_args(b);
   const PlainMap map{k};
   const HeavyList heavy{ns.heavy_q, ns.heavy_bound, ns.counters, ns.heavy_state, ns.state_cap};
-  const unsigned g = grid_for(m, kTravBlock);
+  const unsigned g = grid_for(m, kNearestBlock);
   if (stats)
     return launch("nearest_stats", s, [&] {
-      k_nearest<KIND, FMT, K, true><<<g, kTravBlock, 0, s>>>(t, map, pts, m, order, idx, dist,
+      k_nearest<KIND, FMT, K, true><<<g, kNearestBlock, 0, s>>>(t, map, pts, m, order, idx, dist,
                                                              stats, INT64_MAX, heavy);
     });
   ABX_TRY(fill_u32(ns.counters, 0, 2, s));
   ABX_TRY(launch("nearest", s, [&] {
-    k_nearest<KIND, FMT, K, false><<<g, kTravBlock, 0, s>>>(t, map, pts, m, order, idx, dist,
+    k_nearest<KIND, FMT, K, false><<<g, kNearestBlock, 0, s>>>(t, map, pts, m, order, idx, dist,
                                                             stats, ns.budget, heavy);
   }));
   constexpr int W = coop_waves(K);
