@@ -39,11 +39,14 @@ abx_status launch_wide(int kind, const NodeF32 *src, int64_t ni, const int32_t *
                        hipStream_t s);
 // traverse.hip
 abx_status launch_query_codes(const abx_bvh *b, const float *q, int64_t m, int width,
-                              uint32_t *codes, hipStream_t s);
+                              uint32_t *codes, hipStream_t s, uint32_t *words = nullptr,
+                              uint32_t mark = 0);
 abx_status launch_spatial(const abx_bvh *b, int pred, const float *data, int64_t m,
                           const float *radii, float radius, const int32_t *order, int mode,
                           int32_t *counts, const int32_t *offsets, int32_t *indices, hipStream_t s,
-                          const OnePass *op = nullptr);
+                          const OnePass *op = nullptr, const KeptRows *kept = nullptr);
+abx_status launch_rows_copy(const KeptRows &kept, int64_t m, const int32_t *order,
+                            const int32_t *offsets, int32_t *indices, hipStream_t s);
 abx_status launch_spatial_compact(const OnePass &op, int64_t m, const int32_t *order,
                                   const int32_t *counts, const int32_t *offsets, int32_t *indices,
                                   int32_t *info, int64_t max_count, hipStream_t s);
@@ -85,6 +88,19 @@ abx_status row_offsets(int32_t *off, int64_t m, int32_t k, hipStream_t s) {
   return launch("row_offsets", s, [&] {
     k_row_offsets<<<grid_for(m + 1, 256), 256, 0, s>>>(off, m, k);
   });
+}
+
+// the state words of a spatial search, and the one-pass scheme's overflow flag
+__global__ void k_spatial_begin(uint32_t *words, uint32_t mark, uint32_t *flag) {
+  if (threadIdx.x == 0) {
+    words[0] = mark;
+    words[1] = words[2] = 0;
+    if (flag) flag[0] = 0;
+  }
+}
+
+abx_status spatial_begin(uint32_t *words, uint32_t mark, uint32_t *flag, hipStream_t s) {
+  return launch("spatial_begin", s, [&] { k_spatial_begin<<<1, 64, 0, s>>>(words, mark, flag); });
 }
 
 // ---------------------------------------------------------------- build
@@ -204,12 +220,14 @@ BuildLayout build_layout(const abx_primitives *p, const abx_build_options *o) {
 
 // ---------------------------------------------------------------- queries
 struct QueryLayout {
-  size_t codes, sorted, order, counts, total, scan, sort, heavy_q, heavy_bound, heavy_state, bytes;
+  size_t codes, sorted, order, counts, total, scan, sort, heavy_q, heavy_bound, heavy_state, rows, bytes;
   int64_t state_cap;
+  bool keeps;  // room for kept rows
 };
 
-// `nearest`: also room for the walks heavy nearest queries hand over
-QueryLayout query_layout(int64_t m, bool nearest = false) {
+// `nearest`: also room for the walks heavy nearest queries hand over; `keep`:
+// for the rows a two-pass spatial query keeps
+QueryLayout query_layout(int64_t m, bool nearest = false, bool keep = false) {
   QueryLayout L{};
   const size_t mm = (size_t)m;
   size_t off = 0;
@@ -222,7 +240,7 @@ QueryLayout query_layout(int64_t m, bool nearest = false) {
   L.counts = off;
   off = align_up(off + mm * 4, 256);
   L.total = off;
-  off = align_up(off + 8, 256);
+  off = align_up(off + 24, 256);  // the total, then the spatial search's state words
   L.scan = off;
   off = align_up(off + scan_scratch_bytes(m), 256);
   L.sort = off;
@@ -234,6 +252,9 @@ QueryLayout query_layout(int64_t m, bool nearest = false) {
   L.heavy_state = off;
   L.state_cap = nearest ? heavy_state_cap(m) : 0;
   off = align_up(off + (size_t)L.state_cap * kHeavyStateWords * 4, 256);
+  L.keeps = keep && kept_bytes(m) <= kKeptBytesMax;
+  L.rows = off;
+  off = align_up(off + (L.keeps ? kept_bytes(m) : 0), 256);
   L.bytes = off;
   return L;
 }
@@ -251,15 +272,70 @@ abx_status check_preds(const abx_predicates *p) {
 
 // queries in Morton order: order[] = permutation sorted position -> query
 abx_status order_queries(const abx_bvh *b, const float *data, int64_t m, int width, char *scratch,
-                         const QueryLayout &L, const int32_t **order, hipStream_t s) {
+                         const QueryLayout &L, const int32_t **order, hipStream_t s,
+                         uint32_t *words = nullptr, uint32_t mark = 0) {
   uint32_t *codes = reinterpret_cast<uint32_t *>(scratch + L.codes);
   int32_t *ord = reinterpret_cast<int32_t *>(scratch + L.order);
-  ABX_TRY(launch_query_codes(b, data, m, width, codes, s));
+  ABX_TRY(launch_query_codes(b, data, m, width, codes, s, words, mark));
   ABX_TRY(radix_sort(codes, nullptr, m, 30, scratch + L.sorted, ord, scratch + L.sort,
                      radix_sort_scratch_bytes(m, 30), s));
   ABX_TRY(order_guard(radix_sort_err_word(scratch + L.sort, m, 30), ord, m, s));
   *order = ord;
   return ABX_OK;
+}
+
+// the layout with kept rows if the scratch holds them (they stand last)
+QueryLayout with_kept_rows(const QueryLayout &base, int64_t m, size_t scratch_bytes) {
+  const QueryLayout L = query_layout(m, false, true);
+  return scratch_bytes >= L.bytes ? L : base;
+}
+
+// the state words of a spatial search in its scratch, after the total
+uint32_t *spatial_words(char *sc, const QueryLayout &L) {
+  return reinterpret_cast<uint32_t *>(sc + L.total + 8);
+}
+
+// (the code buffers of the query ordering are free once the order stands, the
+// heavy lists belong to nearest queries)
+KeptRows kept_rows(char *sc, const QueryLayout &L, int64_t m) {
+  KeptRows k;
+  k.buf = reinterpret_cast<int32_t *>(sc + L.rows);
+  k.more = reinterpret_cast<int32_t *>(sc + L.rows + kept_row_bytes(m));
+  k.pool = (int32_t)kept_pool(m);
+  k.counts = reinterpret_cast<int32_t *>(sc + L.sorted);
+  k.ext = reinterpret_cast<int32_t *>(sc + L.heavy_q);
+  k.long_list = reinterpret_cast<int32_t *>(sc + L.codes);
+  k.words = spatial_words(sc, L);
+  return k;
+}
+
+// the total and state words of a finished count pass (blocks the host)
+struct SpatialState {
+  int64_t total;
+  uint32_t mark, longer, extended, pad;
+};
+abx_status read_spatial(const char *sc, const QueryLayout &L, SpatialState *st, hipStream_t s) {
+  ABX_HIP(hipMemcpyAsync(st, sc + L.total, sizeof(*st), hipMemcpyDeviceToHost, s));
+  ABX_HIP(hipStreamSynchronize(s));
+  return ABX_OK;
+}
+
+// the second pass: kept rows copied, longer ones walked again; without kept
+// rows every query walked again
+abx_status spatial_finish(const abx_bvh *bvh, const abx_predicates *p, char *sc, const QueryLayout &L,
+                          const SpatialState &st, const int32_t *offsets, int32_t *indices,
+                          hipStream_t s) {
+  const int32_t *order = p->sort_queries ? reinterpret_cast<const int32_t *>(sc + L.order) : nullptr;
+  const int64_t m = p->m;
+  if (!L.keeps || st.mark != (uint32_t)kKeptRow)
+    return launch_spatial(bvh, p->kind, p->data, m, p->radii, p->radius, order, 1 /*fill*/, nullptr,
+                          offsets, indices, s);
+  const KeptRows kept = kept_rows(sc, L, m);
+  const int64_t longer = std::min<int64_t>(st.longer, m);
+  if (longer < m) ABX_TRY(launch_rows_copy(kept, m, order, offsets, indices, s));
+  if (longer == 0) return ABX_OK;
+  return launch_spatial(bvh, p->kind, p->data, longer, p->radii, p->radius, kept.long_list, 1 /*fill*/,
+                        nullptr, offsets, indices, s);
 }
 
 }  // namespace
@@ -576,7 +652,7 @@ abx_status abx_query_spatial_sizes(const abx_bvh *bvh, const abx_predicates *pre
   ABX_TRY(check_bvh(bvh));
   ABX_TRY(check_preds(preds));
   if (!scratch_bytes) return ABX_ERR_INVALID_ARG;
-  *scratch_bytes = query_layout(preds->m).bytes;
+  *scratch_bytes = query_layout(preds->m, false, true).bytes;
   return ABX_OK;
 }
 
@@ -607,20 +683,30 @@ abx_status abx_query_spatial(const abx_bvh *bvh, const abx_predicates *preds, vo
     ABX_TRY(fill_u32(offsets, 0, (size_t)m + 1, s));
     return ABX_OK;
   }
+  // The first pass keeps each row's first hits, in a scratch with room for them
+  // (a smaller one is walked twice), unless the caller expects most rows to be
+  // longer: a row that fits is copied, not walked for again.
+  L = with_kept_rows(L, m, scratch_bytes);
+  const bool keep = L.keeps && capacity <= (kKeptRow - kKeptRow / 4) * m;
+  const uint32_t mark = keep ? (uint32_t)kKeptRow : 0u;
+  uint32_t *words = spatial_words(sc, L);
   const int32_t *order = nullptr;
-  if (preds->sort_queries) ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s));
+  if (preds->sort_queries)
+    ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s, words, mark));
+  else
+    ABX_TRY(spatial_begin(words, mark, nullptr, s));
+  const KeptRows kept = kept_rows(sc, L, m);
   ABX_TRY(launch_spatial(bvh, preds->kind, preds->data, m, preds->radii, preds->radius, order,
-                         0 /*count*/, counts, nullptr, nullptr, s));
+                         keep ? 4 /*keep*/ : 0 /*count*/, counts, nullptr, nullptr, s, nullptr,
+                         keep ? &kept : nullptr));
   ABX_TRY(exclusive_scan(counts, m, offsets, d_total, sc + L.scan, scan_scratch_bytes(m), s));
-  int64_t t = 0;
-  ABX_HIP(hipMemcpyAsync(&t, d_total, sizeof(t), hipMemcpyDeviceToHost, s));
-  ABX_HIP(hipStreamSynchronize(s));
-  *total = t;
-  if (t >= kMaxCount) return ABX_ERR_OVERFLOW;
-  if (t > capacity) return ABX_ERR_CAPACITY;
-  if (t == 0) return ABX_OK;
-  return launch_spatial(bvh, preds->kind, preds->data, m, preds->radii, preds->radius, order,
-                        1 /*fill*/, nullptr, offsets, indices, s);
+  SpatialState st;
+  ABX_TRY(read_spatial(sc, L, &st, s));
+  *total = st.total;
+  if (st.total >= kMaxCount) return ABX_ERR_OVERFLOW;
+  if (st.total > capacity) return ABX_ERR_CAPACITY;
+  if (st.total == 0) return ABX_OK;
+  return spatial_finish(bvh, preds, sc, L, st, offsets, indices, s);
 }
 
 abx_status abx_query_spatial_fill(const abx_bvh *bvh, const abx_predicates *preds, void *scratch,
@@ -633,14 +719,12 @@ abx_status abx_query_spatial_fill(const abx_bvh *bvh, const abx_predicates *pred
   char *sc = static_cast<char *>(scratch);
   const int64_t m = preds->m;
   if (bvh->n == 0 || m == 0) return ABX_OK;
-  int64_t t = 0;
-  ABX_HIP(hipMemcpyAsync(&t, sc + L.total, sizeof(t), hipMemcpyDeviceToHost, s));
-  ABX_HIP(hipStreamSynchronize(s));
-  if (t > capacity) return ABX_ERR_CAPACITY;
-  if (t == 0) return ABX_OK;
-  const int32_t *order = preds->sort_queries ? reinterpret_cast<const int32_t *>(sc + L.order) : nullptr;
-  return launch_spatial(bvh, preds->kind, preds->data, m, preds->radii, preds->radius, order,
-                        1 /*fill*/, nullptr, offsets, indices, s);
+  SpatialState st;
+  ABX_TRY(read_spatial(sc, L, &st, s));
+  L = with_kept_rows(L, m, scratch_bytes);
+  if (st.total > capacity) return ABX_ERR_CAPACITY;
+  if (st.total == 0) return ABX_OK;
+  return spatial_finish(bvh, preds, sc, L, st, offsets, indices, s);
 }
 
 // ---------------------------------------------------------------- spatial, one pass
@@ -676,7 +760,7 @@ abx_status abx_query_spatial_1p(const abx_bvh *bvh, const abx_predicates *preds,
   uint32_t *flag = reinterpret_cast<uint32_t *>(sc + L.bytes);
   int32_t *buf = reinterpret_cast<int32_t *>(sc + L.bytes + 256);
   const OnePass op{buf, buffer_size, flag, d_total, std::min<int64_t>(capacity, kMaxCount - 1)};
-  ABX_TRY(fill_u32(flag, 0, 4, s));
+  ABX_TRY(spatial_begin(spatial_words(sc, L), 0, flag, s));
   if (bvh->n == 0 || m == 0) {
     ABX_TRY(fill_u32(offsets, 0, (size_t)m + 1, s));
     ABX_TRY(fill_u32(d_total, 0, 2, s));

@@ -94,6 +94,30 @@ inline int64_t heavy_state_cap(int64_t m) {
   return c < kMaxSavedHeavy ? c : kMaxSavedHeavy;
 }
 
+// Rows kept by the first pass of a two-pass spatial query: kKeptRow slots for
+// every query (128 B) and, for the longer rows, extensions of kKeptMore slots
+// from a pool of one for every sixteen queries.  Rows beyond both, and batches
+// whose rows would take more than kKeptBytesMax, are walked twice.
+constexpr int32_t kKeptRow = 32;
+constexpr int32_t kKeptMore = 96;
+constexpr size_t kKeptBytesMax = size_t(8) << 30;
+inline int64_t kept_pool(int64_t m) { return m / 16 + 64; }
+inline size_t kept_row_bytes(int64_t m) { return (size_t)m * kKeptRow * 4; }
+inline size_t kept_bytes(int64_t m) { return kept_row_bytes(m) + (size_t)kept_pool(m) * kKeptMore * 4; }
+
+// Rows the first pass of a two-pass spatial query keeps in the caller's
+// scratch, by sorted position of the query.
+struct KeptRows {
+  int32_t *buf;        // [m * kKeptRow] each row's first hits
+  int32_t *more;       // [pool * kKeptMore] the next ones of longer rows
+  int32_t pool;
+  int32_t *counts;     // [m] hits
+  int32_t *ext;        // [m] rows of more than kKeptRow hits: extension, or -1
+  int32_t *long_list;  // queries whose rows were not kept whole, words[1] of them
+  uint32_t *words;     // [0]: kKeptRow, or 0 if the last pass on this scratch kept no rows;
+                       // [2]: extensions asked for
+};
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---------------------------------------------------------------------------

@@ -70,6 +70,7 @@ struct QueryArgs {
   const float *radii;
   float radius;
   const int32_t *order;  // sorted position -> caller's query index (or null)
+  KeptRows kept;         // keeping pass only
   // one-pass (1P) scheme only
   int32_t *buf;          // [m * bufsize] stored hits, one row per sorted position
   int32_t bufsize;
@@ -258,7 +259,7 @@ __device__ __forceinline__ void stack_pop2(ABX_LDS int32_t *ln, ABX_LDS DT *ld, 
   }
 }
 
-enum { MODE_COUNT = 0, MODE_FILL = 1, MODE_STATS = 2, MODE_STORE = 3 };
+enum { MODE_COUNT = 0, MODE_FILL = 1, MODE_STATS = 2, MODE_STORE = 3, MODE_KEEP = 4 };
 
 // ------------------------------------------------------------------ nearest
 // A candidate (squared distance d, primitive index i) packed into one
