@@ -281,15 +281,14 @@ abx_status abx_query_nearest_static(const abx_bvh *bvh, const float *points /*[m
 /* -- load balance of nearest queries ------------------------------------------
  * A nearest query is first walked by one lane (the paper's batched mode).  A
  * walk that exceeds `visits` internal-node visits is abandoned and the query
- * is answered again by a whole workgroup (16 wavefronts, 8 for k > 16, i.e.
- * 1024 or 512 lanes sharing one query: a breadth-first frontier is split among
- * the lanes, their pruning bound is shared, their candidate lists are merged
- * exactly), starting from the bound the lane had reached.  Results do not
- * depend on the value.  (k > 64 is walked by one lane throughout.)
- * abx_set_nearest_budget sets the process-wide budget (<= 0: unlimited, i.e.
- * one lane per query throughout) and returns the previous one.  Default 22528.
- * A batch of m queries uses min(budget, max(512, m / 24)): small batches
- * leave the GPU idle and hand heavy queries to whole workgroups sooner. */
+ * is taken over by a whole workgroup (128 to 1024 lanes sharing one query: its
+ * unexplored nodes, its candidates and its pruning bound stand in LDS),
+ * starting from where the lane had come.  Results do not depend on the value.
+ * (k > 64 is walked by one lane throughout.)
+ * abx_set_nearest_budget sets the process-wide budget (<= 0: no limit of its
+ * own) and returns the previous one.  Default 8192.  A batch of m queries uses
+ * min(budget, 36 + k + min(m (10 + k) / 6400, 100 + 8 k) + m / 1024): small
+ * batches leave the GPU idle and hand queries to whole workgroups sooner. */
 int64_t abx_set_nearest_budget(int64_t visits);
 
 /* -- traversal statistics ---------------------------------------------------

@@ -39,7 +39,7 @@ abx_status launch_wide(int kind, const NodeF32 *src, int64_t ni, const int32_t *
                        hipStream_t s);
 // traverse.hip
 abx_status launch_query_codes(const abx_bvh *b, const float *q, int64_t m, int width,
-                              uint32_t *codes, hipStream_t s, uint32_t *words = nullptr,
+                              uint32_t *codes, hipStream_t s, uint32_t *words,
                               uint32_t mark = 0);
 abx_status launch_spatial(const abx_bvh *b, int pred, const float *data, int64_t m,
                           const float *radii, float radius, const int32_t *order, int mode,
@@ -52,13 +52,14 @@ abx_status launch_spatial_compact(const OnePass &op, int64_t m, const int32_t *o
                                   int32_t *info, int64_t max_count, hipStream_t s);
 abx_status launch_nearest(const abx_bvh *b, const float *pts, int64_t m, const int32_t *order,
                           int k, int32_t *idx, float *dist, int32_t *stats, int32_t *heavy_q,
-                          float *heavy_bound, uint32_t *counters, int32_t *heavy_state,
+                          float *heavy_bound, int32_t *huge_q, float *huge_bound,
+                          uint32_t *counters, int32_t *heavy_state,
                           int64_t state_cap, int64_t budget, hipStream_t s);
 int max_tree_depth();
 
 // node visits after which a nearest query leaves the one-lane pass for the
 // cooperative pass (abx_set_nearest_budget)
-std::atomic<int64_t> g_nearest_budget{22528};
+std::atomic<int64_t> g_nearest_budget{8192};
 extern std::atomic<uint32_t> g_sort_spin_limit;  // sort.hip
 extern std::atomic<uint32_t> g_fit_table_probes;  // build.hip
 int64_t nearest_budget() { return g_nearest_budget.load(std::memory_order_relaxed); }
@@ -270,13 +271,20 @@ abx_status check_preds(const abx_predicates *p) {
   return ABX_OK;
 }
 
-// queries in Morton order: order[] = permutation sorted position -> query
+// the state words of a spatial search in its scratch, after the total
+uint32_t *spatial_words(char *sc, const QueryLayout &L) {
+  return reinterpret_cast<uint32_t *>(sc + L.total + 8);
+}
+
+// queries in Morton order: order[] = permutation sorted position -> query.
+// Rows that an earlier search kept in this scratch are void from here on
+// (mark 0), unless the caller is the search that keeps its own.
 abx_status order_queries(const abx_bvh *b, const float *data, int64_t m, int width, char *scratch,
                          const QueryLayout &L, const int32_t **order, hipStream_t s,
-                         uint32_t *words = nullptr, uint32_t mark = 0) {
+                         uint32_t mark = 0) {
   uint32_t *codes = reinterpret_cast<uint32_t *>(scratch + L.codes);
   int32_t *ord = reinterpret_cast<int32_t *>(scratch + L.order);
-  ABX_TRY(launch_query_codes(b, data, m, width, codes, s, words, mark));
+  ABX_TRY(launch_query_codes(b, data, m, width, codes, s, spatial_words(scratch, L), mark));
   ABX_TRY(radix_sort(codes, nullptr, m, 30, scratch + L.sorted, ord, scratch + L.sort,
                      radix_sort_scratch_bytes(m, 30), s));
   ABX_TRY(order_guard(radix_sort_err_word(scratch + L.sort, m, 30), ord, m, s));
@@ -288,11 +296,6 @@ abx_status order_queries(const abx_bvh *b, const float *data, int64_t m, int wid
 QueryLayout with_kept_rows(const QueryLayout &base, int64_t m, size_t scratch_bytes) {
   const QueryLayout L = query_layout(m, false, true);
   return scratch_bytes >= L.bytes ? L : base;
-}
-
-// the state words of a spatial search in its scratch, after the total
-uint32_t *spatial_words(char *sc, const QueryLayout &L) {
-  return reinterpret_cast<uint32_t *>(sc + L.total + 8);
 }
 
 // (the code buffers of the query ordering are free once the order stands, the
@@ -389,6 +392,8 @@ abx_status nearest_enqueue(const abx_bvh *bvh, const float *pts, int64_t m, int3
   return launch_nearest(bvh, pts, m, order, (int)kk, indices, dist, nullptr,
                         reinterpret_cast<int32_t *>(sc + L.heavy_q),
                         reinterpret_cast<float *>(sc + L.heavy_bound),
+                        reinterpret_cast<int32_t *>(sc + L.codes),  // (free once sorted)
+                        reinterpret_cast<float *>(sc + L.sorted),
                         reinterpret_cast<uint32_t *>(sc + L.total),
                         reinterpret_cast<int32_t *>(sc + L.heavy_state), L.state_cap, nearest_budget(), s);
 }
@@ -692,7 +697,7 @@ abx_status abx_query_spatial(const abx_bvh *bvh, const abx_predicates *preds, vo
   uint32_t *words = spatial_words(sc, L);
   const int32_t *order = nullptr;
   if (preds->sort_queries)
-    ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s, words, mark));
+    ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s, mark));
   else
     ABX_TRY(spatial_begin(words, mark, nullptr, s));
   const KeptRows kept = kept_rows(sc, L, m);
@@ -832,6 +837,8 @@ static abx_status nearest_common(const abx_bvh *bvh, const float *points, int64_
   return launch_nearest(bvh, points, m, order, (int)kk, indices, distances, stats,
                         reinterpret_cast<int32_t *>(sc + L.heavy_q),
                         reinterpret_cast<float *>(sc + L.heavy_bound),
+                        reinterpret_cast<int32_t *>(sc + L.codes),  // (free once sorted)
+                        reinterpret_cast<float *>(sc + L.sorted),
                         reinterpret_cast<uint32_t *>(sc + L.total),
                         reinterpret_cast<int32_t *>(sc + L.heavy_state), L.state_cap, nearest_budget(), s);
 }

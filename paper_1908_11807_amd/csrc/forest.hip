@@ -373,32 +373,25 @@ abx_status forest_launch_rows(const int64_t *poff, const int64_t *qoff, const in
   });
 }
 
-int coop_grid(int waves);
-int device_cus();
-
 template <int KIND, int FMT, int K>
 abx_status forest_nearest_k(const TreeArgs &t, const ForestMap &map, const float *pts, int64_t M,
-                            const int32_t *order, int32_t *idx, float *dist, const HeavyList &heavy,
+                            const int32_t *order, int32_t *idx, float *dist, const HeavyList &heavy, const HeavyList &huge,
                             uint32_t *queue, int blocks_per_cu, int grab, int64_t budget, hipStream_t s) {
   const unsigned g = (unsigned)std::max(1, device_cus() * blocks_per_cu);
   ABX_TRY(launch("forest_nearest", s, [&] {
     k_forest_nearest<KIND, FMT, K><<<g, kForestBlock, 0, s>>>(t, map, pts, M, order, idx, dist, budget,
                                                              heavy, queue, grab);
   }));
-  return launch("forest_nearest_coop", s, [&] {
-    k_nearest_coop<KIND, FMT, K, ForestMap, coop_waves(K)>
-        <<<(unsigned)coop_grid(coop_waves(K)), CoopShape<coop_waves(K)>::kThreads, 0, s>>>(
-            t, map, pts, idx, dist, heavy);
-  });
+  return launch_coop<KIND, FMT>("forest_nearest_coop", t, map, pts, M, idx, dist, heavy, huge, s);
 }
 
 template <int FMT>
 abx_status forest_nearest_fmt(const TreeArgs &t, const ForestMap &map, const float *pts, int64_t M,
                               const int32_t *order, int k, int32_t *idx, float *dist,
-                              const HeavyList &heavy, uint32_t *queue, int bpc, int grab,
+                              const HeavyList &heavy, const HeavyList &huge, uint32_t *queue, int bpc, int grab,
                               int64_t budget, hipStream_t s) {
 #define ABX_FK(KK) \
-  return forest_nearest_k<ABX_PRIM_POINTS, FMT, KK>(t, map, pts, M, order, idx, dist, heavy, queue, bpc, grab, budget, s)
+  return forest_nearest_k<ABX_PRIM_POINTS, FMT, KK>(t, map, pts, M, order, idx, dist, heavy, huge, queue, bpc, grab, budget, s)
   if (k <= 1) ABX_FK(1);
   if (k <= 2) ABX_FK(2);
   if (k <= 4) ABX_FK(4);
@@ -414,17 +407,19 @@ abx_status forest_nearest_fmt(const TreeArgs &t, const ForestMap &map, const flo
 abx_status forest_launch_nearest(const TreeArgs &t, int format, const int64_t *poff, const int32_t *qtree,
                                  const int32_t *roots, const float *tscene, const int32_t *offsets,
                                  const float *pts, int64_t M, const int32_t *order, int k, int32_t *idx,
-                                 float *dist, int32_t *heavy_q, float *heavy_bound, uint32_t *counters,
+                                 float *dist, int32_t *heavy_q, float *heavy_bound,
+                                 int32_t *huge_q, float *huge_bound, uint32_t *counters,
                                  int blocks_per_cu, int grab, int64_t budget, hipStream_t s) {
   if (M == 0 || k == 0) return ABX_OK;
   if (k > kMaxRegK) return ABX_ERR_UNSUPPORTED;
   const ForestMap map{poff, qtree, roots, tscene, offsets, k};
-  const HeavyList heavy{heavy_q, heavy_bound, counters};
-  ABX_TRY(fill_u32(counters, 0, 3, s));  // heavy count, next heavy, tile queue
+  const HeavyList heavy{heavy_q, heavy_bound, counters}, huge{huge_q, huge_bound, counters + 3};
+  // heavy count, next heavy, tile queue, huge count, next huge
+  ABX_TRY(fill_u32(counters, 0, 5, s));
   if (format == ABX_NODES_FP32)
-    return forest_nearest_fmt<ABX_NODES_FP32>(t, map, pts, M, order, k, idx, dist, heavy, counters + 2,
+    return forest_nearest_fmt<ABX_NODES_FP32>(t, map, pts, M, order, k, idx, dist, heavy, huge, counters + 2,
                                               blocks_per_cu, grab, budget, s);
-  return forest_nearest_fmt<ABX_NODES_Q16>(t, map, pts, M, order, k, idx, dist, heavy, counters + 2,
+  return forest_nearest_fmt<ABX_NODES_Q16>(t, map, pts, M, order, k, idx, dist, heavy, huge, counters + 2,
                                            blocks_per_cu, grab, budget, s);
 }
 

@@ -26,7 +26,8 @@ abx_status forest_launch_rows(const int64_t *poff, const int64_t *qoff, const in
 abx_status forest_launch_nearest(const TreeArgs &t, int format, const int64_t *poff, const int32_t *qtree,
                                  const int32_t *roots, const float *tscene, const int32_t *offsets,
                                  const float *pts, int64_t M, const int32_t *order, int k, int32_t *idx,
-                                 float *dist, int32_t *heavy_q, float *heavy_bound, uint32_t *counters,
+                                 float *dist, int32_t *heavy_q, float *heavy_bound,
+                                 int32_t *huge_q, float *huge_bound, uint32_t *counters,
                                  int blocks_per_cu, int grab, int64_t budget, hipStream_t s);
 abx_status forest_launch_nearest_stats(const TreeArgs &t, int format, const int64_t *poff,
                                        const int32_t *qtree, const int32_t *roots, const float *tscene,
@@ -124,7 +125,7 @@ ForestQueryLayout forest_query_layout(int T, int64_t M) {
   L.base = off;
   off = align_up(off + (size_t)(T + 1) * 8, 256);
   L.counters = off;
-  off = align_up(off + 16, 256);
+  off = align_up(off + 20, 256);
   L.heavy_q = off;
   off = align_up(off + m * 4, 256);
   L.heavy_bound = off;
@@ -333,6 +334,8 @@ abx_status abx_forest_query_nearest(const abx_forest *f, const abx_forest_querie
   return forest_launch_nearest(t, f->format, poff, qtree, roots, tscene, offsets, q->data, M, order, k,
                                indices, distances, reinterpret_cast<int32_t *>(sc + L.heavy_q),
                                reinterpret_cast<float *>(sc + L.heavy_bound),
+                               reinterpret_cast<int32_t *>(sc + L.keys),  // (free once sorted)
+                               reinterpret_cast<float *>(sc + L.sorted),
                                reinterpret_cast<uint32_t *>(sc + L.counters), c.blocks_per_cu,
                                c.tiles_per_grab, c.budget > 0 ? c.budget : INT64_MAX, s);
 }

@@ -440,14 +440,14 @@ __device__ __forceinline__ uint32_t spread10q(uint32_t x) {
   return x;
 }
 
-// `words` (optional): the spatial search's state words, set to (mark, 0, 0).
+// `words`: the spatial search's state words, set to (mark, 0, 0).
 template <int W>
 __global__ __launch_bounds__(kTravBlock) void k_query_codes(const float *__restrict__ q, int64_t m,
                                                             TreeArgs t, uint32_t *__restrict__ codes,
                                                             uint32_t *__restrict__ words,
                                                             uint32_t mark) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (words && i == 0) {
+  if (i == 0) {
     words[0] = mark;
     words[1] = words[2] = 0;
   }
@@ -664,7 +664,9 @@ abx_status launch_spatial_compact(const OnePass &op, int64_t m, const int32_t *o
 struct NearestScratch {
   int32_t *heavy_q;
   float *heavy_bound;
-  uint32_t *counters;  // [0] heavy count, [1] next heavy query
+  int32_t *huge_q;  // those the cooperative pass passes on to larger workgroups
+  float *huge_bound;
+  uint32_t *counters;  // [0] heavy count, [1] next heavy query, [3], [4] the huge ones'
   int64_t budget;
   int32_t *heavy_state;  // saved walks (kHeavyStateWords each), or null
   uint32_t state_cap;
@@ -677,34 +679,27 @@ int device_cus() {
   return cus > 0 ? cus : 256;
 }
 
-// persistent grid of the cooperative pass: as many workgroups as fit at once
-// (LDS bound: a W-wavefront workgroup takes 8 KB per wavefront)
-int coop_grid(int waves) { return device_cus() * std::max(1, 16 / waves); }
-
 template <int KIND, int FMT, int K>
 abx_status nearest_k(const abx_bvh *b, const float *pts, int64_t m, const int32_t *order, int k,
                      int32_t *idx, float *dist, int32_t *stats, const NearestScratch &ns,
                      hipStream_t s) {
   const TreeArgs t = tree_args(b);
   const PlainMap map{k};
-  const HeavyList heavy{ns.heavy_q, ns.heavy_bound, ns.counters, ns.heavy_state, ns.state_cap};
+  const HeavyList heavy{ns.heavy_q, ns.heavy_bound, ns.counters,
+                        saves_walk(K) ? ns.heavy_state : nullptr, ns.state_cap};
   const unsigned g = grid_for(m, kNearestBlock);
   if (stats)
     return launch("nearest_stats", s, [&] {
       k_nearest<KIND, FMT, K, true><<<g, kNearestBlock, 0, s>>>(t, map, pts, m, order, idx, dist,
                                                              stats, INT64_MAX, heavy);
     });
-  ABX_TRY(fill_u32(ns.counters, 0, 2, s));
+  ABX_TRY(fill_u32(ns.counters, 0, 5, s));
   ABX_TRY(launch("nearest", s, [&] {
     k_nearest<KIND, FMT, K, false><<<g, kNearestBlock, 0, s>>>(t, map, pts, m, order, idx, dist,
                                                             stats, ns.budget, heavy);
   }));
-  constexpr int W = coop_waves(K);
-  const unsigned g2 = (unsigned)coop_grid(W);
-  return launch("nearest_coop", s, [&] {
-    k_nearest_coop<KIND, FMT, K, PlainMap, W>
-        <<<g2, CoopShape<W>::kThreads, 0, s>>>(t, map, pts, idx, dist, heavy);
-  });
+  const HeavyList huge{ns.huge_q, ns.huge_bound, ns.counters + 3};
+  return launch_coop<KIND, FMT>("nearest_coop", t, map, pts, m, idx, dist, heavy, huge, s);
 }
 
 template <int KIND, int FMT, bool STATS>
@@ -747,19 +742,31 @@ abx_status nearest_fmt(const abx_bvh *b, const float *pts, int64_t m, const int3
   return nearest_k<KIND, FMT, kMaxRegK>(b, pts, m, order, k, idx, dist, stats, ns, s);
 }
 
-// Small batches leave most of the GPU idle, so their heavy queries are
-// better served early by whole workgroups: the one-lane budget shrinks with
-// the batch (never below 512 visits, never above the configured budget).
-// m / 24 measured best at 1e5 queries on a 1e7-point shell (k = 8: 9.2 ms
-// against 11.5 with m / 16); at 1e4 anything from 512 to 4096 ties.
-int64_t effective_budget(int64_t budget, int64_t m) {
-  const int64_t b = std::max<int64_t>(512, m / 24);
-  return std::min(budget, b);
+// Visits after which a query of a batch of m leaves its lane for a workgroup.
+// A node costs the cooperative pass about as much as the one-lane pass of a
+// full GPU, so what decides is how many queries the other lanes and CUs wait
+// for, and how many short walks would pay for a hand-off they do not need.
+//   36 + k     the least: a bound needs k leaves.  With fewer visits the
+//              workgroup starts without one (1e7 points, 1000 queries, k = 32:
+//              165 us with 64 visits, 495 with 48).
+//   the next   up to what nearly all walks among evenly spread points take
+//              (8k + 100), in step with the batch: up to some 1e4 queries the
+//              GPU has room for workgroups (1e6 points, 1000 queries, k = 10:
+//              132 us against 233 with 512 visits); with 1e5, all of them
+//              handed over at 100 visits took 1150 us instead of 770 (k = 64).
+//   m / 1024   longer walks, as the one-lane pass fills the GPU for longer
+//              (1e7-point shell, k = 10: 1e6 queries 5.7 ms with 1200 to 1800
+//              visits, 9.3 with 8192; 1e7 queries 119 ms with 4096 to 12288,
+//              125 with 22528).
+int64_t effective_budget(int64_t budget, int64_t m, int k) {
+  const int64_t usual = std::min<int64_t>(m * (10 + k) / 6400, 100 + 8 * k);
+  return std::min(budget, 36 + k + usual + m / 1024);
 }
 
 abx_status launch_nearest(const abx_bvh *b, const float *pts, int64_t m, const int32_t *order,
                           int k, int32_t *idx, float *dist, int32_t *stats, int32_t *heavy_q,
-                          float *heavy_bound, uint32_t *counters, int32_t *heavy_state,
+                          float *heavy_bound, int32_t *huge_q, float *huge_bound,
+                          uint32_t *counters, int32_t *heavy_state,
                           int64_t state_cap, int64_t budget, hipStream_t s) {
   if (m == 0 || k == 0) return ABX_OK;
   if (k > kMaxHeapK) return ABX_ERR_UNSUPPORTED;
@@ -777,7 +784,7 @@ abx_status launch_nearest(const abx_bvh *b, const float *pts, int64_t m, const i
   }
   // a 4-wide walk makes about half as many node visits as a binary one
   const int64_t b_eff = b->format == ABX_NODES_Q16W ? std::max<int64_t>(1, budget / 2) : budget;
-  const NearestScratch ns{heavy_q, heavy_bound, counters, effective_budget(b_eff, m), heavy_state,
+  const NearestScratch ns{heavy_q, heavy_bound, huge_q, huge_bound, counters, effective_budget(b_eff, m, k), heavy_state,
                           (uint32_t)std::min<int64_t>(state_cap, kMaxSavedHeavy)};
 #define ABX_FMT(KD, FM) nearest_fmt<KD, FM>(b, pts, m, order, k, idx, dist, stats, ns, s)
   if (b->kind == ABX_PRIM_POINTS) ABX_BY_FORMAT(ABX_FMT, ABX_PRIM_POINTS);

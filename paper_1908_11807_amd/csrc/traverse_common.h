@@ -359,14 +359,12 @@ __device__ __forceinline__ void knn_leaf(const TreeArgs &t, const KnnQuery &q, i
 
 // One step of the nearest walk: visit `node`, offer its leaf children, and
 // return the nearer qualifying internal child (the farther one is pushed),
-// or -1 when neither qualifies.  `bound` is an external upper bound of the
-// final k-th distance, used if BOUNDED.
-template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, bool BOUNDED = true, typename DT>
+// or -1 when neither qualifies.
+template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, typename DT>
 __device__ __forceinline__ int32_t knn_visit2(const TreeArgs &t, const KnnQuery &q, int32_t node,
-                                              float bound, KnnList<K> &L, ABX_LDS int32_t *lds_n,
+                                              KnnList<K> &L, ABX_LDS int32_t *lds_n,
                                               ABX_LDS DT *lds_d, int32_t *ovf_n, DT *ovf_d,
                                               int &sp, int &nl, int32_t &reads) {
-  auto limit = [&]() { return BOUNDED ? fminf(L.kth(), bound) : L.kth(); };
   Kids c;
   load_kids<KIND, FMT>(t, node, c);
   const float dl = box_dist2(c.l[0], c.l[1], c.l[2], c.l[3], c.l[4], c.l[5], q.x, q.y, q.z);
@@ -375,17 +373,17 @@ __device__ __forceinline__ int32_t knn_visit2(const TreeArgs &t, const KnnQuery 
   if (exact_leaf_slots<KIND, FMT>()) {
     // both leaves tested against the bound before either enters the list: one
     // insertion's code runs for whichever child offers
-    const float thr0 = limit();
+    const float thr0 = L.kth();
     const bool ol = ll && dl <= thr0, orr = lr && dr <= thr0;
     if (ol || orr) {
       L.offer_key(ol ? knn_key(dl, ~c.lref) : knn_key(dr, ~c.rref));
       if (ol && orr) L.offer_key(knn_key(dr, ~c.rref));
     }
   } else {
-    if (ll) knn_leaf<KIND, FMT, K>(t, q, ~c.lref, dl, limit(), L, reads);
-    if (lr) knn_leaf<KIND, FMT, K>(t, q, ~c.rref, dr, limit(), L, reads);
+    if (ll) knn_leaf<KIND, FMT, K>(t, q, ~c.lref, dl, L.kth(), L, reads);
+    if (lr) knn_leaf<KIND, FMT, K>(t, q, ~c.rref, dr, L.kth(), L, reads);
   }
-  const float thr = limit();
+  const float thr = L.kth();
   const bool gl = !ll && dl <= thr, gr = !lr && dr <= thr;
   if (gl && gr) {
     // Visit order only (pruning uses the box distances): the child whose box
@@ -458,19 +456,18 @@ __device__ __forceinline__ void wide_slots(const TreeArgs &t, int32_t node, cons
 // the qualifying internal children are visited nearest box centre first:
 // the nearest is returned and the others are pushed farthest first, so they
 // come off the stack in the same order.
-template <int KIND, int K, int B, int S = kLdsDepthNearest, bool BOUNDED = true, typename DT>
+template <int KIND, int K, int B, int S = kLdsDepthNearest, typename DT>
 __device__ __forceinline__ int32_t knn_visit_w(const TreeArgs &t, const KnnQuery &q, int32_t node,
-                                               float bound, KnnList<K> &L, ABX_LDS int32_t *lds_n,
+                                               KnnList<K> &L, ABX_LDS int32_t *lds_n,
                                                ABX_LDS DT *lds_d, int32_t *ovf_n, DT *ovf_d,
                                                int &sp, int &nl, int32_t &reads) {
   // each slot is decoded straight into its box distance and centre key, so
   // the 24 coordinates are never live together (they made the walk spill)
-  auto limit = [&]() { return BOUNDED ? fminf(L.kth(), bound) : L.kth(); };
   float d[4], key[4];
   int32_t r[4];
   wide_slots<KIND>(t, node, q, d, key, r);
   if (exact_leaf_slots<KIND, ABX_NODES_Q16W>()) {
-    const float thr0 = limit();
+    const float thr0 = L.kth();
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (r[j] < 0 && r[j] != kEmptyRef && d[j] <= thr0) L.offer_key(knn_key(d[j], ~r[j]));
@@ -478,9 +475,9 @@ __device__ __forceinline__ int32_t knn_visit_w(const TreeArgs &t, const KnnQuery
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (r[j] < 0 && r[j] != kEmptyRef)
-        knn_leaf<KIND, ABX_NODES_Q16W, K>(t, q, ~r[j], d[j], limit(), L, reads);
+        knn_leaf<KIND, ABX_NODES_Q16W, K>(t, q, ~r[j], d[j], L.kth(), L, reads);
   }
-  const float thr = limit();
+  const float thr = L.kth();
   // the qualifying internal children keep their key; the others sort last
   // with reference -1
 #pragma unroll
@@ -515,17 +512,16 @@ __device__ __forceinline__ int32_t knn_visit_w(const TreeArgs &t, const KnnQuery
   return r[0];
 }
 
-template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, bool BOUNDED = true, typename DT>
+template <int KIND, int FMT, int K, int B, int S = kLdsDepthNearest, typename DT>
 __device__ __forceinline__ int32_t knn_visit(const TreeArgs &t, const KnnQuery &q, int32_t node,
-                                             float bound, KnnList<K> &L, ABX_LDS int32_t *lds_n,
+                                             KnnList<K> &L, ABX_LDS int32_t *lds_n,
                                              ABX_LDS DT *lds_d, int32_t *ovf_n, DT *ovf_d,
                                              int &sp, int &nl, int32_t &reads) {
   if constexpr (FMT == ABX_NODES_Q16W)
-    return knn_visit_w<KIND, K, B, S, BOUNDED>(t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d, sp,
-                                               nl, reads);
+    return knn_visit_w<KIND, K, B, S>(t, q, node, L, lds_n, lds_d, ovf_n, ovf_d, sp, nl, reads);
   else
-    return knn_visit2<KIND, FMT, K, B, S, BOUNDED>(t, q, node, bound, L, lds_n, lds_d, ovf_n, ovf_d,
-                                                   sp, nl, reads);
+    return knn_visit2<KIND, FMT, K, B, S>(t, q, node, L, lds_n, lds_d, ovf_n, ovf_d, sp, nl,
+                                          reads);
 }
 
 // pop deferred nodes until one still qualifies; -1 when the stack runs dry
@@ -576,10 +572,14 @@ __device__ __forceinline__ void knn_write(const KnnList<K> &L, int k, int32_t ba
   }
 }
 
+// Lists of more than 32 keys are not saved, their walks restart from the root:
+// the save code's registers made them spill (48 keys: 9 -> 525 spill accesses).
+constexpr bool saves_walk(int K) { return K <= 32; }
+
 struct HeavyList {
-  int32_t *q;          // caller's query index
-  float *bound;        // k-th distance reached before the hand-off
-  uint32_t *count;     // [0] entries, [1] next entry to serve
+  int32_t *q = nullptr;      // caller's query index
+  float *bound = nullptr;    // k-th distance reached before the hand-off
+  uint32_t *count = nullptr; // [0] entries, [1] next entry to serve
   int32_t *state = nullptr;  // saved walks, kHeavyStateWords words each (optional)
   uint32_t state_cap = 0;    // entries below this keep their walk
 };
@@ -619,7 +619,7 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
     done = false;
     for (int64_t it = 0; it < limit; ++it) {
       if (STATS) ++visited;
-      node = knn_visit<KIND, FMT, K, B, kWin, false>(t, q, node, INFINITY, L, lds_n, lds_d, ovf_n,
+      node = knn_visit<KIND, FMT, K, B, kWin>(t, q, node, L, lds_n, lds_d, ovf_n,
                                                      ovf_d, sp, nl, reads);
       if (node < 0) node = knn_pop<B, kWin>(L.kth(), lds_n, lds_d, ovf_n, ovf_d, sp, nl);
       if (node < 0) {
@@ -633,9 +633,7 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
       heavy.bound[h] = L.kth();
       // the walk so far: the next node (not yet visited), the unexplored
       // subtrees on the stack, the candidates; the workgroup resumes it.
-      // Lists of more than 32 keys restart instead: the save code's
-      // registers made their walk spill (48 keys: 9 -> 525 spill accesses).
-      if (K <= 32 && heavy.state && h < heavy.state_cap) {
+      if (saves_walk(K) && heavy.state && h < heavy.state_cap) {
         int32_t *st = heavy.state + (int64_t)h * kHeavyStateWords;
         if (sp + 1 > kHeavyStateEntries) {
           st[0] = -1;  // too deep to save: the workgroup restarts from the root
@@ -652,6 +650,7 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
             ++c;
           }
           st[0] = c;
+          st[1] = K;
           int64_t *keys = reinterpret_cast<int64_t *>(st + 2 + 2 * kHeavyStateEntries);
 #pragma unroll
           for (int j = 0; j < K; ++j) keys[j] = L.key[j];
@@ -668,296 +667,301 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
   knn_write<K>(L, info.kk, info.base, indices + info.out, dist + info.out);
 }
 
-__device__ __forceinline__ float wave_min(float v) {
+// Pass 2: a workgroup of T threads per heavy query.  The unexplored nodes
+// stand in one LDS stack for the workgroup; a step takes a node per thread off
+// its top, and the children that still qualify go back on top.  So every
+// thread has a node as long as the stack has enough, whatever the shape of the
+// subtrees, and the stack grows as a depth-first walk's does.  Candidates
+// within the shared bound gather in LDS as well.  Once kCoopSlack more than k
+// stand there, each one's rank among them is counted: the k best stay, in
+// order, and the k-th distance is the new bound -- that of all the primitives
+// the workgroup has met.  At the end the same step leaves the row.
+// What bounds it: the latency of a step (one node load and two barriers) for a
+// single query; for many, the cache lines of their nodes, which neighbouring
+// queries no longer share.
+// (A breadth-first frontier split among 1024 threads, each walking its share
+// depth-first with a list and a bound of its own, left 38 % of their time idle
+// and took 42 of 105 us a query to grow.  1e7-point shell, k = 10, 38 000
+// heavy queries of 1e7: 20.3 ms that way, 7.1 to 10.4 this way; 1e5 queries of
+// k = 32 in all: 14.4 ms, now 3.6.)
+//
+// A step over `take` entries adds at most (A - 1) * take to the stack, so a
+// take of (free - kCoopReserve) / A leaves the reserve free, and single ones,
+// a depth-first walk, need no more than the reserve (60 levels of three
+// siblings, or 120 of one; taller trees are refused).
+constexpr int kCoopSlack = 32;
+constexpr int kCoopRank = 128;  // candidates ranked at a time, more than any k
+constexpr int kCoopReserve = 192;
+constexpr int coop_stack(int A, int T) { return (A == 4 ? 14 : 16) * T; }
+constexpr int coop_found(int A, int T) { return kMaxRegK + kCoopSlack + A * T; }
+// Steps of a small workgroup after which a query goes on to one of
+// kCoopLarge threads (from the root again, with the bound reached): the few
+// heaviest would end alone.  256 to 2048 measured alike.
+constexpr int64_t kCoopSteps = 512;
+static_assert(kMaxRegK + kCoopSlack < kCoopRank, "a step's few are ranked at once");
+
+// Order the candidates found so far and drop those beyond the k-th; `bound`
+// (float bits) becomes the k-th distance if there are k.  More than kCoopRank
+// are thinned first, by the k-th of the first kCoopRank.  Called by the whole
+// workgroup, after a barrier that makes the candidates visible.
+template <int A, int T>
+__device__ __forceinline__ void coop_rank(int64_t *cand, uint32_t *found, uint32_t *bound,
+                                          int64_t *pivot, int k) {
+  constexpr int kPer = (coop_found(A, T) + T - 1) / T;
+  constexpr int kOne = (kCoopRank + T - 1) / T;
+  const int tid = threadIdx.x;
+  while (true) {
+    const int n = (int)*found, some = min(n, kCoopRank);
+    int64_t key[kOne];
+    int rank[kOne];
 #pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
-  return v;
+    for (int r = 0; r < kOne; ++r) {
+      const bool in = r * T + tid < some;
+      key[r] = in ? cand[r * T + tid] : 0;
+      rank[r] = in ? 0 : kCoopRank;
+    }
+    if (tid < some) {
+#pragma unroll 4
+      for (int e = 0; e < some; ++e) {
+        const int64_t x = cand[e];
+#pragma unroll
+        for (int r = 0; r < kOne; ++r) rank[r] += x < key[r] ? 1 : 0;
+      }
+    }
+    if (n <= kCoopRank) {
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kOne; ++r) {
+        if (rank[r] < k) cand[rank[r]] = key[r];  // (keys differ: one entry per primitive)
+        if (rank[r] == k - 1) atomicMin(bound, __float_as_uint(key_dist(key[r])));
+      }
+      if (tid == 0) *found = (uint32_t)min(n, k);
+      __syncthreads();
+      return;
+    }
+    int64_t own[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+      const int i = r * T + tid;
+      own[r] = i < n ? cand[i] : INT64_MAX;
+    }
+#pragma unroll
+    for (int r = 0; r < kOne; ++r)
+      if (rank[r] == k - 1) *pivot = key[r];
+    __syncthreads();
+    if (tid == 0) *found = 0;
+    const int64_t most = *pivot;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPer; ++r)
+      if (own[r] <= most) cand[atomicAdd(found, 1u)] = own[r];
+    __syncthreads();
+  }
 }
 
-// wavefronts per heavy query: 16 (the heaviest query of a batch bounds the
-// launch, so its walk is split 1024 ways); 8 for k > 16, whose lists need
-// more registers than a 1024-thread workgroup leaves per lane
-constexpr int coop_waves(int K) { return K > 16 ? 8 : 16; }
-
-// the depth-first phase shares the workgroup's bound every 2^kCoopShareLog2
-// steps: a fresher bound prunes more, sharing costs a wave-wide minimum and
-// an LDS atomic per wave
-constexpr int kCoopShareLog2 = 3;
-
-// Pass 2: a workgroup of W wavefronts per heavy query.  The launch lasts as
-// long as its heaviest query, whose walk is split W*64 ways.  The workgroup
-// expands the tree breadth-first until the frontier holds 256*W nodes, then
-// thread i walks frontier entries i, i + 64W, ... depth-first with its own
-// stack and candidate list.  The threads share the smallest of their k-th
-// distances through LDS (each is the k-th distance of k real primitives, so
-// it bounds the final k-th distance from above) and prune with it.  Every
-// primitive of the final result lives in the list of the thread that met it,
-// so the k best of all lists, taken in (distance, index) order, are the
-// exact answer: each wavefront merges its 64 lists, then the first merges
-// the W results.  Runs as a persistent grid draining the heavy list.
-template <int W, int A = 2>
-struct CoopShape {
-  static constexpr int kThreads = W * kWave;
-  static constexpr int kCap = 512 * W;       // entries of a frontier buffer
-  static constexpr int kFront = kCap / A;    // frontier size at which the threads split up:
-                                             // one expansion of A-ary nodes stays below kCap
-  static constexpr int kWindow = kCap / kThreads;  // LDS stack entries per thread
-};
-
-// LDS float minimum through the unsigned bit pattern (values are >= 0)
-__device__ __forceinline__ void lds_min(uint32_t *p, float v) {
-  atomicMin(p, __float_as_uint(v));
-}
-
-template <int KIND, int FMT, int K, class Map, int W>
-__global__ __launch_bounds__(CoopShape<W>::kThreads) void k_nearest_coop(
+template <int KIND, int FMT, class Map, int T>
+__global__ __launch_bounds__(T) void k_nearest_coop(
     TreeArgs t, Map map, const float *__restrict__ pts, int32_t *__restrict__ indices,
-    float *__restrict__ dist, HeavyList heavy) {
-  using S = CoopShape<W, FMT == ABX_NODES_Q16W ? 4 : 2>;
-  static_assert(kHeavyStateEntries < S::kFront, "a saved walk fits the first frontier");
-  // two frontier buffers; during the depth-first phase the one not holding
-  // the final frontier is the threads' stack window
-  __shared__ int32_t s_fn[2][S::kCap];
-  __shared__ float s_fd[2][S::kCap];
-  __shared__ int64_t s_best[W][K];
-  __shared__ uint32_t s_size[2], s_bound, s_h;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    float *__restrict__ dist, HeavyList heavy,
+    HeavyList huge) {
+  constexpr int A = FMT == ABX_NODES_Q16W ? 4 : 2;  // children of a node
+  constexpr int kCap = coop_stack(A, T);
+  static_assert(kHeavyStateEntries + kCoopReserve + A * T <= kCap, "a saved walk fits");
+  __shared__ int32_t s_node[kCap];
+  __shared__ float s_dist[kCap];
+  __shared__ int64_t s_cand[coop_found(A, T)];
+  __shared__ int64_t s_pivot;
+  __shared__ uint32_t s_add[3], s_bound, s_found, s_h;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const uint32_t total = heavy.count[0];
+  // the first query by the workgroup's number (2048 empty workgroups that each
+  // drew one took 17 us), the next ones as they come
+  uint32_t h = blockIdx.x;
+  if (h >= total) return;
   resolve_qframe(t);
-  int32_t reads = 0;
-  while (true) {
+  for (bool first = true;; first = false) {
     __syncthreads();  // the previous query's buffers are free again
-    if (tid == 0) s_h = atomicAdd(heavy.count + 1, 1u);
-    __syncthreads();
-    const uint32_t h = s_h;
-    if (h >= total) break;
+    if (!first) {
+      if (tid == 0) s_h = gridDim.x + atomicAdd(heavy.count + 1, 1u);
+      __syncthreads();
+      h = s_h;
+      if (h >= total) break;
+    }
     const int32_t qi = heavy.q[h];
     const QInfo info = map.info(qi, t);
     const int k = info.kk;
     const KnnQuery q{pts[3 * (int64_t)qi], pts[3 * (int64_t)qi + 1], pts[3 * (int64_t)qi + 2]};
-    KnnList<K> L;
-    L.init(k);
     // start from the walk the lane saved (its unexplored subtrees, and its
-    // candidates in thread 0's list), else from the root
-    int fsize = 1;
-    // (lists of more than 32 keys never save their walk)
-    const int32_t *st = K <= 32 && heavy.state && h < heavy.state_cap
-                            ? heavy.state + (int64_t)h * kHeavyStateWords
-                            : nullptr;
+    // candidates), else from the root
+    int size = 1;
+    const int32_t *st =
+        heavy.state && h < heavy.state_cap ? heavy.state + (int64_t)h * kHeavyStateWords : nullptr;
     int c = st ? min(st[0], kHeavyStateEntries) : -1;
     {
       // every saved node must be an internal node, else restart from the root
       bool bad = false;
-      for (int e = tid; e < c; e += S::kThreads) {
+      for (int e = tid; e < c; e += T) {
         const int32_t nd = st[2 + 2 * e];
         bad |= nd < 0 || nd >= t.nint;
       }
       if (__syncthreads_or(bad)) c = -1;
     }
+    if (tid == 0) {
+      s_bound = __float_as_uint(heavy.bound[h]);
+      s_add[0] = 0;
+      s_found = 0;
+    }
+    __syncthreads();
     if (c >= 1) {
-      for (int e = tid; e < c; e += S::kThreads) {
-        s_fn[0][e] = st[2 + 2 * e];
-        s_fd[0][e] = __int_as_float(st[3 + 2 * e]);
+      for (int e = tid; e < c; e += T) {
+        s_node[e] = st[2 + 2 * e];
+        s_dist[e] = __int_as_float(st[3 + 2 * e]);
       }
-      fsize = c;
-      if (tid == 0) {
-        const int64_t *keys = reinterpret_cast<const int64_t *>(st + 2 + 2 * kHeavyStateEntries);
-#pragma unroll
-        for (int j = 0; j < K; ++j) L.key[j] = keys[j];
-      }
+      size = c;
+      const int64_t *keys = reinterpret_cast<const int64_t *>(st + 2 + 2 * kHeavyStateEntries);
+      if (tid < st[1] && keys[tid] >= 0 && keys[tid] != kKeyEmpty)
+        s_cand[atomicAdd(&s_found, 1u)] = keys[tid];
     } else if (tid == 0) {
-      s_fn[0][0] = info.root;
-      s_fd[0][0] = 0.0f;
+      s_node[0] = info.root;
+      s_dist[0] = 0.0f;
     }
-    if (tid == 0) s_bound = __float_as_uint(heavy.bound[h]);
     __syncthreads();
 
-    // breadth-first expansion of the frontier
-    int cur = 0;
-    while (fsize > 0 && fsize < S::kFront) {
-      // the size of the next frontier counts into s_size[cur ^ 1], last read
-      // before the previous level's closing barrier
-      if (tid == 0) s_size[cur ^ 1] = 0;
-      __syncthreads();
+    // (without a list to hand on to, the bound on the steps only guarantees the end)
+    const int64_t most = huge.q ? kCoopSteps : 4 * t.n + 64;
+    int turn = 0, after = 1;  // this step's counter and the next one's, of three
+    for (int64_t step = 0; size > 0 && step < most; ++step) {
+      const int room = kCap - size;
+      const int take = min(size, min(T, max(1, (room - kCoopReserve) / A)));
+      const int base = size - take;
+      bool ek[A];
+      int32_t rk[A];
+      float dk[A];
+#pragma unroll
+      for (int j = 0; j < A; ++j) {
+        ek[j] = false;
+        rk[j] = 0;
+        dk[j] = 0.0f;
+      }
       const float bnd = __uint_as_float(s_bound);
-      for (int base = 0; base < fsize; base += S::kThreads) {
-        const int e = base + tid;
-        if constexpr (FMT == ABX_NODES_Q16W) {
-          bool ek[4] = {false, false, false, false};
-          int32_t rk[4] = {0, 0, 0, 0};
-          float dk[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-          if (e < fsize && s_fd[cur][e] <= fminf(L.kth(), bnd)) {
-            Kids4 c;
-            load_kids4<KIND>(t, s_fn[cur][e], c);
+      if (tid < take && s_dist[base + tid] <= bnd) {
+        const int32_t node = s_node[base + tid];
+        if constexpr (A == 4) {
+          Kids4 c4;
+          load_kids4<KIND>(t, node, c4);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              dk[j] = c.ref[j] == kEmptyRef ? INFINITY
-                                            : box_dist2(c.b[j][0], c.b[j][1], c.b[j][2], c.b[j][3],
-                                                        c.b[j][4], c.b[j][5], q.x, q.y, q.z);
-              if (c.ref[j] < 0 && c.ref[j] != kEmptyRef)
-                knn_leaf<KIND, FMT, K>(t, q, ~c.ref[j], dk[j], fminf(L.kth(), bnd), L, reads);
-            }
-            const float thr = fminf(L.kth(), bnd);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              ek[j] = c.ref[j] >= 0 && dk[j] <= thr;
-              rk[j] = c.ref[j];
-            }
+          for (int j = 0; j < A; ++j) {
+            rk[j] = c4.ref[j];
+            dk[j] = rk[j] == kEmptyRef ? INFINITY
+                                       : box_dist2(c4.b[j][0], c4.b[j][1], c4.b[j][2], c4.b[j][3],
+                                                   c4.b[j][4], c4.b[j][5], q.x, q.y, q.z);
           }
-          uint64_t bk[4];
-          int cnt = 0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            bk[j] = __ballot(ek[j]);
-            cnt += __popcll(bk[j]);
-          }
-          uint32_t o = 0;
-          if (lane == 0 && cnt > 0) o = atomicAdd(&s_size[cur ^ 1], (uint32_t)cnt);
-          int at0 = (int)__shfl(o, 0, kWave);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (ek[j]) {
-              const int at = at0 + __popcll(bk[j] & lt);
-              s_fn[cur ^ 1][at] = rk[j];
-              s_fd[cur ^ 1][at] = dk[j];
-            }
-            at0 += __popcll(bk[j]);
-          }
-          continue;
-        }
-        bool el = false, er = false;
-        int32_t lref = 0, rref = 0;
-        float dl = 0.0f, dr = 0.0f;
-        if (e < fsize && s_fd[cur][e] <= fminf(L.kth(), bnd)) {
-          Kids c;
-          load_kids<KIND, FMT>(t, s_fn[cur][e], c);
-          dl = box_dist2(c.l[0], c.l[1], c.l[2], c.l[3], c.l[4], c.l[5], q.x, q.y, q.z);
-          dr = box_dist2(c.r[0], c.r[1], c.r[2], c.r[3], c.r[4], c.r[5], q.x, q.y, q.z);
-          if (c.lref < 0) knn_leaf<KIND, FMT, K>(t, q, ~c.lref, dl, fminf(L.kth(), bnd), L, reads);
-          if (c.rref < 0) knn_leaf<KIND, FMT, K>(t, q, ~c.rref, dr, fminf(L.kth(), bnd), L, reads);
-          const float thr = fminf(L.kth(), bnd);
-          el = c.lref >= 0 && dl <= thr;
-          er = c.rref >= 0 && dr <= thr;
-          lref = c.lref;
-          rref = c.rref;
-        }
-        // wave-level compaction, one LDS reservation per wave
-        const uint64_t bl = __ballot(el), br = __ballot(er);
-        const int cl = __popcll(bl), cnt = cl + __popcll(br);
-        uint32_t o = 0;
-        if (lane == 0 && cnt > 0) o = atomicAdd(&s_size[cur ^ 1], (uint32_t)cnt);
-        o = __shfl(o, 0, kWave);
-        if (el) {
-          const int at = (int)o + __popcll(bl & lt);
-          s_fn[cur ^ 1][at] = lref;
-          s_fd[cur ^ 1][at] = dl;
-        }
-        if (er) {
-          const int at = (int)o + cl + __popcll(br & lt);
-          s_fn[cur ^ 1][at] = rref;
-          s_fd[cur ^ 1][at] = dr;
-        }
-      }
-      const float wm = wave_min(L.kth());
-      if (lane == 0) lds_min(&s_bound, wm);
-      __syncthreads();
-      cur ^= 1;
-      fsize = (int)s_size[cur];
-    }
-
-    // depth-first walks of the thread's share of the frontier
-    int32_t ovf_n[kMaxDepth];
-    float ovf_d[kMaxDepth];
-    ABX_LDS int32_t *lds_n = (ABX_LDS int32_t *)(s_fn[cur ^ 1]) + tid;
-    ABX_LDS float *lds_d = (ABX_LDS float *)(s_fd[cur ^ 1]) + tid;
-    int sp = 0, nl = 0;
-    const int mine = fsize > tid ? (fsize - 1 - tid) / S::kThreads + 1 : 0;
-    for (int a = mine - 1; a >= 0; --a)
-      stack_push2<S::kWindow, S::kThreads>(lds_n, lds_d, ovf_n, ovf_d, sp, nl,
-                                           s_fn[cur][tid + S::kThreads * a],
-                                           s_fd[cur][tid + S::kThreads * a]);
-    __syncthreads();
-    bool active = true;
-    int32_t node = -1;
-    float bound = __uint_as_float(s_bound);
-    for (int64_t it = 0; it < 4 * t.n + 64; ++it) {
-      // share the workgroup's bound (each lane also prunes with its own list)
-      if ((it & ((1 << kCoopShareLog2) - 1)) == 0) {
-        const float wm = wave_min(fminf(bound, L.kth()));
-        if (lane == 0) lds_min(&s_bound, wm);
-        bound = fminf(wm, __uint_as_float(s_bound));
-      }
-      if (!__any(active)) break;
-      if (active) {
-        if (node < 0)
-          node = knn_pop<S::kThreads, S::kWindow>(fminf(L.kth(), bound), lds_n, lds_d, ovf_n,
-                                                  ovf_d, sp, nl);
-        if (node < 0) {
-          active = false;
         } else {
-          node = knn_visit<KIND, FMT, K, S::kThreads, S::kWindow>(t, q, node, bound, L, lds_n, lds_d,
-                                                                  ovf_n, ovf_d, sp, nl, reads);
+          Kids c2;
+          load_kids<KIND, FMT>(t, node, c2);
+          rk[0] = c2.lref;
+          rk[1] = c2.rref;
+          dk[0] = box_dist2(c2.l[0], c2.l[1], c2.l[2], c2.l[3], c2.l[4], c2.l[5], q.x, q.y, q.z);
+          dk[1] = box_dist2(c2.r[0], c2.r[1], c2.r[2], c2.r[3], c2.r[4], c2.r[5], q.x, q.y, q.z);
+        }
+#pragma unroll
+        for (int j = 0; j < A; ++j) {
+          ek[j] = rk[j] >= 0 && dk[j] <= bnd;
+          if (rk[j] < 0 && rk[j] != kEmptyRef && dk[j] <= bnd) {
+            float d = dk[j];
+            if (!exact_leaf_slots<KIND, FMT>()) {
+              float b[6];
+              load_leaf_box(t, ~rk[j], b);
+              d = box_dist2(b[0], b[1], b[2], b[3], b[4], b[5], q.x, q.y, q.z);
+            }
+            if (d <= bnd) s_cand[atomicAdd(&s_found, 1u)] = knn_key(d, ~rk[j]);
+          }
         }
       }
+      // the counter of the next step: last read two barriers ago
+      if (tid == 0) s_add[after] = 0;
+      __syncthreads();  // the entries taken have been read, the candidates written
+      const int found = (int)s_found;
+      // wave-level compaction, one LDS reservation per wave
+      uint64_t bk[A];
+      int cnt = 0;
+#pragma unroll
+      for (int j = 0; j < A; ++j) {
+        bk[j] = __ballot(ek[j]);
+        cnt += __popcll(bk[j]);
+      }
+      uint32_t o = 0;
+      if (lane == 0 && cnt > 0) o = atomicAdd(&s_add[turn], (uint32_t)cnt);
+      int at = base + (int)__shfl(o, 0, kWave);
+#pragma unroll
+      for (int j = 0; j < A; ++j) {
+        if (ek[j]) {
+          const int to = at + __popcll(bk[j] & lt);
+          s_node[to] = rk[j];
+          s_dist[to] = dk[j];
+        }
+        at += __popcll(bk[j]);
+      }
+      __syncthreads();
+      size = base + (int)s_add[turn];
+      turn = after;
+      after = after == 2 ? 0 : after + 1;
+      if (found > k + kCoopSlack) coop_rank<A, T>(s_cand, &s_found, &s_bound, &s_pivot, k);
     }
 
-    // merge: each wave takes the k best of its 64 lists (k rounds of a
-    // wave-wide minimum over the list fronts), then wave 0 the k best of the
-    // W wave results
-    for (int s2 = 0; s2 < K - k; ++s2) L.shift();
-    for (int j = 0; j < k; ++j) {
-      int64_t m = L.key[0];
-#pragma unroll
-      for (int o = kWave / 2; o > 0; o >>= 1) {
-        const int64_t m2 = __shfl_xor(m, o, kWave);
-        m = m2 < m ? m2 : m;
+    coop_rank<A, T>(s_cand, &s_found, &s_bound, &s_pivot, k);
+    if (size > 0 && huge.q) {
+      if (tid == 0) {
+        const uint32_t e = atomicAdd(huge.count, 1u);
+        huge.q[e] = qi;
+        huge.bound[e] = __uint_as_float(s_bound);
       }
-      // keys are unique (one entry per primitive), so exactly one lane
-      // holds the minimum
-      if (L.key[0] == m) L.shift();
-      if (lane == 0) s_best[wv][j] = m;
+      continue;
     }
-    __syncthreads();
-    if (wv == 0) {
-      // candidates c = lane, lane + 64, ... of the W*k wave results
-      constexpr int kPer = (W * K + kWave - 1) / kWave;
-      int64_t mine_c[kPer];
-#pragma unroll
-      for (int a = 0; a < kPer; ++a) {
-        const int c = lane + kWave * a;
-        mine_c[a] = c < W * k ? s_best[c / k][c % k] : kKeyEmpty;
-      }
-      int64_t out = 0;
-      for (int j = 0; j < k; ++j) {
-        int64_t lo = mine_c[0];
-        int at = 0;
-#pragma unroll
-        for (int a = 1; a < kPer; ++a)
-          if (mine_c[a] < lo) {
-            lo = mine_c[a];
-            at = a;
-          }
-        int64_t m = lo;
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) {
-          const int64_t m2 = __shfl_xor(m, o, kWave);
-          m = m2 < m ? m2 : m;
-        }
-        if (lo == m) {
-#pragma unroll
-          for (int a = 0; a < kPer; ++a)
-            if (a == at) mine_c[a] = kKeyEmpty;
-        }
-        if (lane == j) out = m;
-      }
-      if (lane < k) {
-        indices[info.out + lane] = key_index(out) - info.base;
-        dist[info.out + lane] = sqrtf(key_dist(out));
-      }
+    if (tid < k) {
+      const int64_t key = tid < (int)s_found ? s_cand[tid] : kKeyEmpty;
+      indices[info.out + tid] = key_index(key) - info.base;
+      dist[info.out + tid] = sqrtf(key_dist(key));
     }
   }
-  (void)reads;
+}
+
+// Threads a query: as many as one CU holds while there is a CU for each query
+// (1e7-point shell, 100 queries, k = 10: 117 us against 142 with 128), fewer
+// for more queries, which fill the GPU with less of the barriers between (4000
+// queries: 247 us with 256, 508 with 1024; 1e5 of k = 32: 3.4 ms with 128,
+// 4.5 with 256, 4.0 with 64).
+constexpr int kCoopLarge = 1024;
+constexpr int kCoopMiddle = 256;
+constexpr int kCoopSmall = 128;
+
+int device_cus();
+
+// The heavy queries of a batch of m (the grids hold as many workgroups as fit
+// a CU at once: about 150 B of LDS a thread).
+template <int KIND, int FMT, class Map>
+abx_status launch_coop(const char *name, const TreeArgs &t, const Map &map, const float *pts, int64_t m,
+                       int32_t *idx, float *dist, const HeavyList &heavy, const HeavyList &huge,
+                       hipStream_t s) {
+  const int cus = device_cus();
+  if (m <= cus)
+    return launch(name, s, [&] {
+      k_nearest_coop<KIND, FMT, Map, kCoopLarge>
+          <<<(unsigned)m, kCoopLarge, 0, s>>>(t, map, pts, idx, dist, heavy, HeavyList{});
+    });
+  ABX_TRY(launch(name, s, [&] {
+    if (m <= 16 * (int64_t)cus)
+      k_nearest_coop<KIND, FMT, Map, kCoopMiddle>
+          <<<(unsigned)(cus * 4), kCoopMiddle, 0, s>>>(t, map, pts, idx, dist, heavy, huge);
+    else
+      k_nearest_coop<KIND, FMT, Map, kCoopSmall>
+          <<<(unsigned)(cus * 8), kCoopSmall, 0, s>>>(t, map, pts, idx, dist, heavy, huge);
+  }));
+  return launch(name, s, [&] {
+    k_nearest_coop<KIND, FMT, Map, kCoopLarge>
+        <<<(unsigned)cus, kCoopLarge, 0, s>>>(t, map, pts, idx, dist, huge, HeavyList{});
+  });
 }
 
 }  // namespace abx
