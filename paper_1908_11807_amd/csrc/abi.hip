@@ -889,6 +889,7 @@ abx_status abx_radix_sort_check(const void *scratch, int64_t n, int32_t key_bits
   if (n <= 1) return ABX_OK;
   if (!scratch) return ABX_ERR_INVALID_ARG;
   const uint32_t *w = radix_sort_err_word(const_cast<void *>(scratch), n, key_bits);
+  if (!w) return ABX_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   uint32_t v = 0;
   ABX_HIP(hipMemcpyAsync(&v, w, sizeof(v), hipMemcpyDeviceToHost, s));

@@ -59,9 +59,40 @@ static_assert(kRadix == kBlock, "one digit per thread");
 
 int num_passes(int key_bits) { return (key_bits + kRadixBits - 1) / kRadixBits; }
 
-__device__ __forceinline__ uint64_t lanemask_lt() {
-  const int lane = threadIdx.x & (kWave - 1);
-  return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+// lanes of `m` below the calling one
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
+// The lanes among those with `ok` that hold the same digit.  All kRadixBits are
+// compared, also where a digit has fewer (the others are zero everywhere): a
+// loop over their number took 14 instructions a bit, with a branch and the
+// waits of a serial chain, where five do (1e7 keys: 79.5 -> 78 us a pass of
+// 64-bit keys, 72 -> 70 of 32-bit ones; the sort of 1e4 keys by one workgroup
+// 43 -> 35 us with it and the ranks taken without a broadcast).
+__device__ __forceinline__ uint64_t same_digit(uint32_t d, bool ok) {
+  const uint64_t in = __ballot(ok);
+  uint32_t lo = (uint32_t)in, hi = (uint32_t)(in >> 32);
+#pragma unroll
+  for (int b = 0; b < kRadixBits; ++b) {
+    const int32_t bit = __builtin_amdgcn_sbfe((int32_t)d, b, 1);  // all ones or zeros
+    const uint64_t bb = __builtin_amdgcn_ballot_w64(bit != 0);
+    lo &= ~((uint32_t)bb ^ (uint32_t)bit);
+    hi &= ~((uint32_t)(bb >> 32) ^ (uint32_t)bit);
+  }
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Rank of a lane's key among the wave's keys of its digit so far, whose number
+// `count` holds: every lane of `m` reads it before the lowest of them raises it
+// (a wavefront's LDS accesses stay in order).
+__device__ __forceinline__ uint32_t take_ranks(uint32_t *count, uint64_t m, bool ok) {
+  const uint32_t below = lanes_below(m);
+  const uint32_t old = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  if (ok && below == 0)
+    __hip_atomic_store(count, old + (uint32_t)__popcll(m), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WAVEFRONT);
+  return old + below;
 }
 
 // exclusive scan of one value per thread over a B-thread block
@@ -184,28 +215,14 @@ __global__ __launch_bounds__(kSweepOf<K>) void k_onesweep(const K *__restrict__ 
                        __HIP_MEMORY_SCOPE_AGENT);
 
   // Wave ranking: lanes holding the same digit find each other through one
-  // ballot per digit bit; the lowest such lane bumps the wave's running
-  // count for the digit and broadcasts the old value.
-  const uint64_t lt = lanemask_lt();
+  // ballot per digit bit.
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     const int64_t i = wbase + r * kWave + lane;
     const bool ok = i < n;
     const uint32_t d = (uint32_t)(k[r] >> shift) & dmask;
-    uint64_t m = __ballot(ok);
-    for (int b = 0; b < nbits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      m &= bit ? bb : ~bb;
-    }
-    const int leader = ok ? (__ffsll((unsigned long long)m) - 1) : 0;
-    uint32_t old = 0;
-    if (ok && lane == leader) {
-      old = s_cnt[wave][d];
-      s_cnt[wave][d] = old + (uint32_t)__popcll(m);
-    }
-    old = __shfl(old, leader, kWave);
-    rank[r] = old + (uint32_t)__popcll(m & lt);
+    const uint64_t m = same_digit(d, ok);
+    rank[r] = take_ranks(&s_cnt[wave][d], m, ok);
   }
   __syncthreads();
 
@@ -298,6 +315,96 @@ __global__ __launch_bounds__(kSweepOf<K>) void k_onesweep(const K *__restrict__ 
   }
 }
 
+// Up to kSmallMax pairs in one launch: a workgroup keeps the keys in registers
+// and passes them through LDS once a digit, ranked as in k_onesweep; the
+// values follow as source positions and are read at the end.  A small sort was
+// bound by its launches (a fill, the histograms, their scan and 4 or 8 passes),
+// each on one to three of the 256 CUs; now by the ranking, 60 instructions a
+// key and digit on one CU.  63 bits: 1000 keys 70 -> 17 us, 1e4 92 -> 68;
+// 30 bits: 35 -> 13 and 47 -> 35.  The line lies at 12 keys a thread, where
+// the two meet (12 288 keys: 80 us against 87, 40 against 44), short of the
+// LDS of a CU.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallMax = 12 * kSmallThreads;
+
+template <typename K, int kItems>
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(const K *__restrict__ kin,
+                                                              const int32_t *__restrict__ vin,
+                                                              K *__restrict__ kout,
+                                                              int32_t *__restrict__ vout, int n,
+                                                              int key_bits) {
+  constexpr int kT = kSmallThreads, kW = kT / kWave;
+  __shared__ uint32_t s_cnt[kW][kRadix];
+  __shared__ uint32_t s_loc[kRadix];
+  __shared__ uint32_t s_tmp[kW];
+  __shared__ K s_keys[kT * kItems];
+  __shared__ uint16_t s_from[kT * kItems];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int base = wave * (kItems * kWave) + lane;  // a wavefront's keys follow one another
+  K k[kItems];
+  uint16_t from[kItems];
+  uint32_t rank[kItems];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const int i = base + r * kWave;
+    const bool ok = i < n;
+    k[r] = ok ? kin[i] : (K)0;
+    from[r] = (uint16_t)i;
+  }
+  for (int shift = 0; shift < key_bits; shift += kRadixBits) {
+    const int nbits = min(kRadixBits, key_bits - shift);
+    const uint32_t dmask = (1u << nbits) - 1u;
+    for (int i = tid; i < kW * kRadix; i += kT) (&s_cnt[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const bool ok = base + r * kWave < n;
+      const uint32_t d = (uint32_t)(k[r] >> shift) & dmask;
+      const uint64_t m = same_digit(d, ok);
+      rank[r] = take_ranks(&s_cnt[wave][d], m, ok);
+    }
+    __syncthreads();
+    uint32_t total = 0;
+    if (tid < kRadix) {
+#pragma unroll
+      for (int w = 0; w < kW; ++w) {
+        const uint32_t x = s_cnt[w][tid];
+        s_cnt[w][tid] = total;
+        total += x;
+      }
+    }
+    const uint32_t loc = block_exclusive_scan<kT>(total, s_tmp);
+    if (tid < kRadix) s_loc[tid] = loc;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      if (base + r * kWave < n) {
+        const uint32_t d = (uint32_t)(k[r] >> shift) & dmask;
+        const uint32_t pos = s_loc[d] + s_cnt[wave][d] + rank[r];
+        s_keys[pos] = k[r];
+        s_from[pos] = from[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const int i = base + r * kWave;
+      if (i < n) {
+        k[r] = s_keys[i];
+        from[r] = s_from[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const int i = base + r * kWave;
+    if (i < n) {
+      kout[i] = k[r];
+      vout[i] = vin ? vin[from[r]] : (int32_t)from[r];
+    }
+  }
+}
+
 template <typename K>
 __global__ void k_copy_pairs(const K *__restrict__ kin, const int32_t *__restrict__ vin,
                              K *__restrict__ kout, int32_t *__restrict__ vout, int64_t n) {
@@ -363,6 +470,19 @@ abx_status sort_impl(const K *kin, const int32_t *vin, int64_t n, int key_bits, 
       }));
     return ABX_OK;
   }
+  if (n <= kSmallMax)
+    return launch("sort_small", s, [&] {
+#define ABX_SMALL(I) \
+  if (n <= I * kSmallThreads) return k_sort_small<K, I><<<1, kSmallThreads, 0, s>>>(kin, vin, kout, vout, (int)n, key_bits)
+      ABX_SMALL(1);
+      ABX_SMALL(2);
+      ABX_SMALL(4);
+      ABX_SMALL(6);
+      ABX_SMALL(8);
+      ABX_SMALL(10);
+      ABX_SMALL(12);
+#undef ABX_SMALL
+    });
   const SortLayout L = sort_layout(n, key_bits);
   uint32_t *hist = reinterpret_cast<uint32_t *>(scratch + L.hist);
   uint32_t *ctr = reinterpret_cast<uint32_t *>(scratch + L.ctr);
@@ -427,7 +547,7 @@ abx_status order_guard(const uint32_t *err, int32_t *order, int64_t m, hipStream
 }
 
 uint32_t *radix_sort_err_word(void *scratch, int64_t n, int key_bits) {
-  if (n <= 1) return nullptr;  // no look-back: nothing can give up
+  if (n <= kSmallMax) return nullptr;  // no look-back: nothing can give up
   return reinterpret_cast<uint32_t *>(static_cast<char *>(scratch) + sort_layout(n, key_bits).err);
 }
 
