@@ -49,10 +49,11 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
                                                         int32_t *__restrict__ out_counts,
                                                         const int32_t *__restrict__ offsets,
                                                         int32_t *__restrict__ indices) {
-  // keeping pass: half the window, the other half holds hits
-  constexpr int kWin = MODE == MODE_KEEP ? kLdsDepthSpatial / 2 : kLdsDepthSpatial;
+  // passes that write hits: half the window, the other half holds them
+  constexpr bool kHolds = MODE == MODE_KEEP || MODE == MODE_STORE || MODE == MODE_FILL;
+  constexpr int kWin = kHolds ? kLdsDepthSpatial / 2 : kLdsDepthSpatial;
   __shared__ int32_t s_stack[kWin * kSpatialBlock];
-  __shared__ int32_t s_held[MODE == MODE_KEEP ? 8 * kSpatialBlock : 1];
+  __shared__ int32_t s_held[kHolds ? 8 * kSpatialBlock : 1];
   const int64_t tq = xcd_tile(blockIdx.x, gridDim.x) * kSpatialBlock + threadIdx.x;
   if (tq >= qa.m) return;
   // the fill pass of the one-pass scheme runs only after an overflow, and
@@ -82,11 +83,12 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
                                                : 0;
   int32_t cnt = 0, visited = 0, leaf_reads = 0;
 
-  // Kept rows: hits collect in LDS and leave eight at a time.  (A store per
-  // hit would stand between a visit and the wait for its node, as loads and
-  // stores retire in order: 446 us that way for 1e6 queries of ten hits on
-  // 1e6 points, 386 this way; counting alone takes 346, and the second walk
-  // that the kept rows make unnecessary took 404.)
+  // Hits collect in LDS and leave eight at a time.  (A store per hit would
+  // stand between a visit and the wait for its node, as loads and stores
+  // retire in order: 1e6 queries of ten hits on 1e6 points, rows kept, 446 us
+  // that way and 386 this way; counting alone takes 346, and the second walk
+  // that the kept rows make unnecessary took 404.  The storing pass of the
+  // one-pass search, 32 slots a row: 294 -> 270 us.)
   ABX_LDS int32_t *held = (ABX_LDS int32_t *)(s_held) + threadIdx.x;
   int32_t ext = -1;
   auto keep = [&](int32_t at) {  // hits at .. at + 7 of the row
@@ -106,6 +108,19 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
     t4[1] = make_int4(held[4 * kSpatialBlock], held[5 * kSpatialBlock], held[6 * kSpatialBlock], held[7 * kSpatialBlock]);
   };
 
+  auto put = [&](int32_t at) {  // the same hits, in their place in `out`
+    // (rows start anywhere: 16 B stores of 4 B alignment)
+    typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(4)));
+    if (cnt >= at + 8 && at + 8 <= row_len) {
+      int4u *to = reinterpret_cast<int4u *>(out + at);
+      to[0] = int4u{held[0], held[kSpatialBlock], held[2 * kSpatialBlock], held[3 * kSpatialBlock]};
+      to[1] = int4u{held[4 * kSpatialBlock], held[5 * kSpatialBlock], held[6 * kSpatialBlock], held[7 * kSpatialBlock]};
+    } else {
+      const int32_t end = cnt < row_len ? cnt : row_len;
+      for (int j = 0; at + j < end; ++j) out[at + j] = held[j * kSpatialBlock];
+    }
+  };
+
   // a leaf child (primitive idx) whose node-stored box passed: confirm where
   // the slot is quantised, and emit
   auto leaf = [&](int32_t idx) {
@@ -115,10 +130,12 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
       if (MODE == MODE_STATS) ++leaf_reads;
       if (!q.test(b)) return;
     }
-    if ((MODE == MODE_FILL || MODE == MODE_STORE) && cnt < row_len) out[cnt] = idx;
-    if (MODE == MODE_KEEP) held[(cnt & 7) * kSpatialBlock] = idx;
+    if (kHolds) held[(cnt & 7) * kSpatialBlock] = idx;
     ++cnt;
-    if (MODE == MODE_KEEP && (cnt & 7) == 0) keep(cnt - 8);
+    if (kHolds && (cnt & 7) == 0) {
+      if (MODE == MODE_KEEP) keep(cnt - 8);
+      else put(cnt - 8);
+    }
   };
 
   if (t.n == 1) {
@@ -175,6 +192,7 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
     }
   }
   if (MODE == MODE_COUNT || MODE == MODE_STORE || MODE == MODE_KEEP) out_counts[qi] = cnt;
+  if ((MODE == MODE_STORE || MODE == MODE_FILL) && (cnt & 7)) put(cnt & ~7);
   if (MODE == MODE_KEEP) {
     if (cnt & 7) keep(cnt & ~7);
     qa.kept.counts[tq] = cnt;
@@ -592,8 +610,8 @@ __global__ __launch_bounds__(kTravBlock) void k_spatial_compact(const int32_t *_
 // ------------------------------------------------------------ kept rows
 // The second pass of the two-pass scheme when the first one kept the rows
 // (radius search, 1e6 queries of ten hits: 922 -> 600 us a call; box overlaps
-// of 1e6 boxes, build included, 1490 -> 1150 us): each is copied to its place (those not kept whole are walked again, from the
-// list the first pass made).  Eight lanes a row read 16 B each, neighbouring
+// of 1e6 boxes, build included, 1490 -> 1150 us): each is copied to its place
+// (those not kept whole are walked again, from the list the first pass made).  Eight lanes a row read 16 B each, neighbouring
 // rows one after another; the counts tell an empty row without touching its
 // slots.
 __global__ __launch_bounds__(kTravBlock) void k_rows_copy(KeptRows kept, int64_t m,

@@ -109,3 +109,19 @@ def test_pool_of_extensions_runs_out():
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
     off, idx = abx.query_spatial(t, q, radius=0.25, sort_queries=False)
     assert torch.equal(want[0], off) and torch.equal(want[1], idx)
+
+
+@pytest.mark.parametrize("fmt", ["fp32", "q16w"])
+@pytest.mark.parametrize("buffer", [1, 7, 8, 9, 16, 23, 64])
+def test_one_pass_rows_end_anywhere(fmt, buffer):
+    # rows of 0 to 40 hits against buffers that end inside, at and beyond a
+    # group of eight: stored rows, and the second walk after an overflow, equal
+    # the two-pass rows entry for entry
+    pts = torch.arange(41, dtype=torch.float32, device="cuda")[:, None].repeat(1, 3) * 0.01
+    q = torch.zeros(200, 3, device="cuda")
+    radii = torch.arange(200, dtype=torch.float32, device="cuda") * (0.01 * 3 ** 0.5 * 0.21)
+    t = abx.bvh_build(pts, node_format=fmt)
+    off, idx = abx.query_spatial(t, q, radii=radii)
+    assert {int(c) for c in (off[1:] - off[:-1])} >= set(range(1, 41))
+    o1, x1, _ = abx.query_spatial_1p(t, q, buffer, radii=radii)
+    assert torch.equal(o1, off) and torch.equal(x1[:idx.numel()], idx)
