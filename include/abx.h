@@ -194,11 +194,14 @@ abx_status abx_bvh_get_layout(const abx_bvh *bvh, abx_bvh_layout *out /*host*/);
  *   query by a stack traversal, scans the counts into offsets[0..m] (rows in
  *   the caller's query order, offsets[0] = 0, offsets[m] = total), and
  *   blocks the host to read the total into *total.  If total <= capacity it
- *   traverses again, writing each row's primitive indices (order within a
- *   row unspecified), and returns ABX_OK.  Otherwise it returns
+ *   writes each row's primitive indices (order within a row unspecified) and
+ *   returns ABX_OK: from the rows the first traversal kept, if the scratch has
+ *   the room that abx_query_spatial_sizes asks for and capacity is at most 24
+ *   entries a query, else by traversing again (so do rows too long to keep; a
+ *   smaller scratch, without that room, is accepted).  Otherwise it returns
  *   ABX_ERR_CAPACITY with offsets and *total valid; the caller may then call
  *   abx_query_spatial_fill with a large enough `indices` and the same
- *   scratch (which keeps the query order).  total >= 2^31 gives
+ *   scratch (which keeps the query order and rows).  total >= 2^31 gives
  *   ABX_ERR_OVERFLOW.  The user-side estimate `capacity` plays the role of
  *   the paper's buffer_size (section 2.3).
  * abx_query_spatial_fill: the second pass alone, after a call of

@@ -120,8 +120,8 @@ struct BuildLayout {
 };
 
 // 4-wide trees: a walk pushes up to three children per level of half as many
-// levels, so the stacks (kMaxDepth entries, 8 of them for the cooperative
-// pass's share of its frontier) bound the binary height at 78
+// levels, so the stacks (kMaxDepth entries, 8 of them to spare) bound the
+// binary height at 78
 bool height_fits(int64_t height, bool wide, int max_depth) {
   const int64_t need = wide ? 3 * ((height + 1) / 2) : height;
   return need + 8 < max_depth;
@@ -597,8 +597,8 @@ abx_status abx_bvh_build(const abx_primitives *prims, const abx_build_options *o
   if (h.bad & 4) return ABX_ERR_UNSUPPORTED;  // refit bound exceeded (malformed hierarchy)
   if (h.bad & 8) return ABX_ERR_UNSUPPORTED;  // depth-first order out of range (too deep)
   if ((h.bad & 2) && L.q16) return ABX_ERR_UNSUPPORTED;
-  // traversal stacks hold at most height + 8 entries (8 = the cooperative
-  // pass's share of the initial frontier); 4-wide walks more per level
+  // traversal stacks hold the height and 8 entries to spare (the cooperative
+  // pass's reserve counts on this limit); 4-wide walks more per level
   if (!height_fits(h.height, L.wnodes, max_tree_depth())) return ABX_ERR_UNSUPPORTED;
 
   abx_bvh *b = new (std::nothrow) abx_bvh;
