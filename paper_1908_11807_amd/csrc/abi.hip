@@ -277,14 +277,15 @@ uint32_t *spatial_words(char *sc, const QueryLayout &L) {
 }
 
 // queries in Morton order: order[] = permutation sorted position -> query.
-// Rows that an earlier search kept in this scratch are void from here on
-// (mark 0), unless the caller is the search that keeps its own.
+// The scratch then holds that order and nothing of an earlier search (`kept`:
+// and the rows that the caller, a spatial search, is about to keep).
 abx_status order_queries(const abx_bvh *b, const float *data, int64_t m, int width, char *scratch,
                          const QueryLayout &L, const int32_t **order, hipStream_t s,
-                         uint32_t mark = 0) {
+                         uint32_t kept = 0) {
   uint32_t *codes = reinterpret_cast<uint32_t *>(scratch + L.codes);
   int32_t *ord = reinterpret_cast<int32_t *>(scratch + L.order);
-  ABX_TRY(launch_query_codes(b, data, m, width, codes, s, spatial_words(scratch, L), mark));
+  ABX_TRY(launch_query_codes(b, data, m, width, codes, s, spatial_words(scratch, L),
+                             kScratchTag | kScratchOrdered | kept));
   ABX_TRY(radix_sort(codes, nullptr, m, 30, scratch + L.sorted, ord, scratch + L.sort,
                      radix_sort_scratch_bytes(m, 30), s));
   ABX_TRY(order_guard(radix_sort_err_word(scratch + L.sort, m, 30), ord, m, s));
@@ -323,14 +324,17 @@ abx_status read_spatial(const char *sc, const QueryLayout &L, SpatialState *st, 
   return ABX_OK;
 }
 
-// the second pass: kept rows copied, longer ones walked again; without kept
-// rows every query walked again
+// The second pass: kept rows copied, longer ones walked again; without kept
+// rows every query walked again.  The rows lie in the order the first pass
+// walked in, so that pass's order counts (st.mark), not p->sort_queries.
 abx_status spatial_finish(const abx_bvh *bvh, const abx_predicates *p, char *sc, const QueryLayout &L,
                           const SpatialState &st, const int32_t *offsets, int32_t *indices,
                           hipStream_t s) {
-  const int32_t *order = p->sort_queries ? reinterpret_cast<const int32_t *>(sc + L.order) : nullptr;
+  const uint32_t what = (st.mark & ~3u) == kScratchTag ? st.mark : 0u;
+  const int32_t *order =
+      what & kScratchOrdered ? reinterpret_cast<const int32_t *>(sc + L.order) : nullptr;
   const int64_t m = p->m;
-  if (!L.keeps || st.mark != (uint32_t)kKeptRow)
+  if (!L.keeps || !(what & kScratchKept))
     return launch_spatial(bvh, p->kind, p->data, m, p->radii, p->radius, order, 1 /*fill*/, nullptr,
                           offsets, indices, s);
   const KeptRows kept = kept_rows(sc, L, m);
@@ -693,13 +697,13 @@ abx_status abx_query_spatial(const abx_bvh *bvh, const abx_predicates *preds, vo
   // longer: a row that fits is copied, not walked for again.
   L = with_kept_rows(L, m, scratch_bytes);
   const bool keep = L.keeps && capacity <= (kKeptRow - kKeptRow / 4) * m;
-  const uint32_t mark = keep ? (uint32_t)kKeptRow : 0u;
+  const uint32_t mark = keep ? kScratchKept : 0u;
   uint32_t *words = spatial_words(sc, L);
   const int32_t *order = nullptr;
   if (preds->sort_queries)
     ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s, mark));
   else
-    ABX_TRY(spatial_begin(words, mark, nullptr, s));
+    ABX_TRY(spatial_begin(words, kScratchTag | mark, nullptr, s));
   const KeptRows kept = kept_rows(sc, L, m);
   ABX_TRY(launch_spatial(bvh, preds->kind, preds->data, m, preds->radii, preds->radius, order,
                          keep ? 4 /*keep*/ : 0 /*count*/, counts, nullptr, nullptr, s, nullptr,

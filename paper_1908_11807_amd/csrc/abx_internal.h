@@ -114,9 +114,15 @@ struct KeptRows {
   int32_t *counts;     // [m] hits
   int32_t *ext;        // [m] rows of more than kKeptRow hits: extension, or -1
   int32_t *long_list;  // queries whose rows were not kept whole, words[1] of them
-  uint32_t *words;     // [0]: kKeptRow, or 0 if the last pass on this scratch kept no rows;
-                       // [2]: extensions asked for
+  uint32_t *words;     // [0]: what stands in this scratch (kScratch...); [2]: extensions asked for
 };
+
+// Word [0]: what the last search of queries left in the scratch, for the fill
+// that may follow.  Without the tag nothing does (a fill then walks every query
+// in the caller's order, which needs no state).
+constexpr uint32_t kScratchTag = 0x5ca7c400u;
+constexpr uint32_t kScratchOrdered = 1u;  // the query order
+constexpr uint32_t kScratchKept = 2u;     // rows, by position in that order (or by query without one)
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

@@ -613,7 +613,7 @@ __global__ __launch_bounds__(kTravBlock) void k_spatial_compact(const int32_t *_
 // of 1e6 boxes, build included, 1490 -> 1150 us): each is copied to its place
 // (those not kept whole are walked again, from the list the first pass made).  Eight lanes a row read 16 B each, neighbouring
 // rows one after another; the counts tell an empty row without touching its
-// slots.
+// slots.  No more is written of a row than its offsets give it.
 __global__ __launch_bounds__(kTravBlock) void k_rows_copy(KeptRows kept, int64_t m,
                                                           const int32_t *__restrict__ order,
                                                           const int32_t *__restrict__ offsets,
@@ -623,15 +623,17 @@ __global__ __launch_bounds__(kTravBlock) void k_rows_copy(KeptRows kept, int64_t
   const int64_t tq = id / kLanes;
   const int l = (int)(id & (kLanes - 1));
   if (tq >= m) return;
-  const int32_t c = kept.counts[tq];
-  if (4 * l >= c) return;
+  const int32_t hits = kept.counts[tq];
+  if (4 * l >= hits) return;
   int32_t ext = -1;
-  if (c > kKeptRow) {
+  if (hits > kKeptRow) {
     ext = kept.ext[tq];
     if (ext < 0) return;
   }
   const int64_t qi = order ? order[tq] : tq;
-  int32_t *out = indices + offsets[qi];
+  const int32_t at = offsets[qi], c = min(hits, offsets[qi + 1] - at);
+  if (4 * l >= c) return;
+  int32_t *out = indices + at;
   const int4 *from = reinterpret_cast<const int4 *>(kept.buf + tq * kKeptRow);
   for (int32_t e = 4 * l;;) {
     const int4 v = from[l];

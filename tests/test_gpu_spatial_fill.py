@@ -1,0 +1,81 @@
+"""The second pass of a two-pass spatial search, called by itself: it gives the
+rows of the search that stands in the scratch, whatever order its own
+predicates ask for, and writes no more of a row than the offsets give it."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1908_11807_amd import abx, datagen
+
+pytestmark = pytest.mark.gpu
+
+VP = C.c_void_p
+N, M = 4000, 1500
+RADIUS = 0.16     # about 60 hits inside the cube: rows kept whole, extended and walked again
+
+
+def stream():
+    return VP(torch.cuda.current_stream().cuda_stream)
+
+
+@pytest.fixture(scope="module")
+def setup():
+    t = abx.bvh_build(torch.from_numpy(datagen.uniform_cube(N, 1)).cuda(), node_format="q16")
+    q = torch.from_numpy(datagen.uniform_cube(M, 2)).cuda()
+    off, idx = abx.query_spatial(t, q, radius=RADIUS, capacity=N * M // 4)   # walked twice
+    return t, q, off, idx
+
+
+def scratch_for(t, q):
+    b = C.c_size_t()
+    pr = abx.Predicates(abx.PRED_WITHIN, q.data_ptr(), M, None, RADIUS, 1)
+    assert abx.library().abx_query_spatial_sizes(t.handle, C.byref(pr), C.byref(b)) == abx.OK
+    return torch.full((b.value,), 0x5a, dtype=torch.uint8, device="cuda")
+
+
+def count(t, q, scratch, sort, radius=RADIUS):
+    """The first pass with no room for results: offsets and total."""
+    pr = abx.Predicates(abx.PRED_WITHIN, q.data_ptr(), M, None, radius, sort)
+    off = torch.empty(M + 1, dtype=torch.int32, device="cuda")
+    total = C.c_int64()
+    assert abx.library().abx_query_spatial(t.handle, C.byref(pr), VP(scratch.data_ptr()),
+                                           scratch.numel(), VP(off.data_ptr()), None, 0,
+                                           C.byref(total), stream()) == abx.ERR_CAPACITY
+    return off, total.value
+
+
+def fill(t, q, scratch, sort, off, total, radius=RADIUS):
+    pr = abx.Predicates(abx.PRED_WITHIN, q.data_ptr(), M, None, radius, sort)
+    idx = torch.full((total,), -7, dtype=torch.int32, device="cuda")
+    assert abx.library().abx_query_spatial_fill(t.handle, C.byref(pr), VP(scratch.data_ptr()),
+                                                scratch.numel(), VP(off.data_ptr()),
+                                                VP(idx.data_ptr()), total, stream()) == abx.OK
+    return idx
+
+
+@pytest.mark.parametrize("searched", [0, 1])
+@pytest.mark.parametrize("filled", [0, 1])
+def test_fill_follows_the_searchs_order(setup, searched, filled):
+    t, q, off, idx = setup
+    sc = scratch_for(t, q)
+    got_off, total = count(t, q, sc, searched)
+    assert torch.equal(got_off, off)
+    assert torch.equal(fill(t, q, sc, filled, off, total), idx)
+
+
+def test_rows_end_where_their_offsets_do(setup):
+    # a caller that wants up to `most` hits a query
+    t, q, off, idx = setup
+    sc = scratch_for(t, q)
+    _, total = count(t, q, sc, 1)
+    full = np.diff(off.cpu().numpy())
+    for most in (0, 1, 5, 32, 33, 100):
+        short = np.minimum(full, most)
+        cut = torch.from_numpy(np.concatenate([[0], np.cumsum(short)]).astype(np.int32)).cuda()
+        got = fill(t, q, sc, 1, cut, total).cpu().numpy()
+        want = np.concatenate([idx.cpu().numpy()[o:o + c]
+                               for o, c in zip(off.cpu().numpy(), short)])
+        assert np.array_equal(got[:len(want)], want)
+        assert (got[len(want):] == -7).all()      # nothing beyond the last row
