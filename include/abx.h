@@ -288,8 +288,9 @@ abx_status abx_query_nearest_static(const abx_bvh *bvh, const float *points /*[m
  * unexplored nodes, its candidates and its pruning bound stand in LDS),
  * starting from where the lane had come.  Results do not depend on the value.
  * (k > 64 is walked by one lane throughout.)
- * abx_set_nearest_budget sets the process-wide budget (<= 0: no limit of its
- * own) and returns the previous one.  Default 8192.  A batch of m queries uses
+ * abx_set_nearest_budget sets the process-wide budget (<= 0: unlimited, i.e.
+ * one lane per query throughout) and returns the previous one (INT64_MAX:
+ * unlimited).  Default 8192.  With a limit, a batch of m queries uses
  * min(budget, 36 + k + min(m (10 + k) / 6400, 100 + 8 k) + m / 1024): small
  * batches leave the GPU idle and hand queries to whole workgroups sooner. */
 int64_t abx_set_nearest_budget(int64_t visits);
