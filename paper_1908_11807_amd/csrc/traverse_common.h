@@ -672,10 +672,15 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
 // its top, and the children that still qualify go back on top.  So every
 // thread has a node as long as the stack has enough, whatever the shape of the
 // subtrees, and the stack grows as a depth-first walk's does.  Candidates
-// within the shared bound gather in LDS as well.  Once kCoopSlack more than k
+// before the shared bound gather in LDS as well.  Once kCoopSlack more than k
 // stand there, each one's rank among them is counted: the k best stay, in
-// order, and the k-th distance is the new bound -- that of all the primitives
-// the workgroup has met.  At the end the same step leaves the row.
+// order, and the k-th is the new bound -- that of all the primitives the
+// workgroup has met.  The bound is a whole key, distance and index: by its
+// distance alone, every primitive at the k-th distance would stand there again
+// and again (1e6 equal points, 1000 queries: 25 ms that way, 10 this way).
+// The lower child goes on top, so that indices which only their order in the
+// tree separates come in ascending order, the best first.  At the end the same
+// step leaves the row.
 // What bounds it: the latency of a step (one node load and two barriers) for a
 // single query; for many, the cache lines of their nodes, which neighbouring
 // queries no longer share.
@@ -701,11 +706,12 @@ constexpr int64_t kCoopSteps = 512;
 static_assert(kMaxRegK + kCoopSlack < kCoopRank, "a step's few are ranked at once");
 
 // Order the candidates found so far and drop those beyond the k-th; `bound`
-// (float bits) becomes the k-th distance if there are k.  More than kCoopRank
+// becomes the k-th key if there are k (every candidate precedes the bound it
+// was taken under, so it only ever falls).  More than kCoopRank
 // are thinned first, by the k-th of the first kCoopRank.  Called by the whole
 // workgroup, after a barrier that makes the candidates visible.
 template <int A, int T>
-__device__ __forceinline__ void coop_rank(int64_t *cand, uint32_t *found, uint32_t *bound,
+__device__ __forceinline__ void coop_rank(int64_t *cand, uint32_t *found, int64_t *bound,
                                           int64_t *pivot, int k) {
   constexpr int kPer = (coop_found(A, T) + T - 1) / T;
   constexpr int kOne = (kCoopRank + T - 1) / T;
@@ -733,7 +739,7 @@ __device__ __forceinline__ void coop_rank(int64_t *cand, uint32_t *found, uint32
 #pragma unroll
       for (int r = 0; r < kOne; ++r) {
         if (rank[r] < k) cand[rank[r]] = key[r];  // (keys differ: one entry per primitive)
-        if (rank[r] == k - 1) atomicMin(bound, __float_as_uint(key_dist(key[r])));
+        if (rank[r] == k - 1) *bound = key[r];
       }
       if (tid == 0) *found = (uint32_t)min(n, k);
       __syncthreads();
@@ -770,8 +776,8 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
   __shared__ int32_t s_node[kCap];
   __shared__ float s_dist[kCap];
   __shared__ int64_t s_cand[coop_found(A, T)];
-  __shared__ int64_t s_pivot;
-  __shared__ uint32_t s_add[3], s_bound, s_found, s_h;
+  __shared__ int64_t s_pivot, s_bound;
+  __shared__ uint32_t s_add[3], s_found, s_h;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const uint32_t total = heavy.count[0];
@@ -808,7 +814,7 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
       if (__syncthreads_or(bad)) c = -1;
     }
     if (tid == 0) {
-      s_bound = __float_as_uint(heavy.bound[h]);
+      s_bound = knn_key(heavy.bound[h], INT32_MAX);  // (no primitive's index)
       s_add[0] = 0;
       s_found = 0;
     }
@@ -844,7 +850,8 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
         rk[j] = 0;
         dk[j] = 0.0f;
       }
-      const float bnd = __uint_as_float(s_bound);
+      const int64_t kth = s_bound;
+      const float bnd = key_dist(kth);
       if (tid < take && s_dist[base + tid] <= bnd) {
         const int32_t node = s_node[base + tid];
         if constexpr (A == 4) {
@@ -875,7 +882,9 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
               load_leaf_box(t, ~rk[j], b);
               d = box_dist2(b[0], b[1], b[2], b[3], b[4], b[5], q.x, q.y, q.z);
             }
-            if (d <= bnd) s_cand[atomicAdd(&s_found, 1u)] = knn_key(d, ~rk[j]);
+            // (a NaN distance follows every bound)
+            const int64_t key = knn_key(d, ~rk[j]);
+            if (key < kth) s_cand[atomicAdd(&s_found, 1u)] = key;
           }
         }
       }
@@ -883,25 +892,25 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
       if (tid == 0) s_add[after] = 0;
       __syncthreads();  // the entries taken have been read, the candidates written
       const int found = (int)s_found;
-      // wave-level compaction, one LDS reservation per wave
-      uint64_t bk[A];
-      int cnt = 0;
+      // wave-level compaction, one LDS reservation per wave; a lane's children
+      // follow the lower lanes' ones, the first child last
+      int cnt = 0, at = base;
 #pragma unroll
       for (int j = 0; j < A; ++j) {
-        bk[j] = __ballot(ek[j]);
-        cnt += __popcll(bk[j]);
+        const uint64_t bk = __ballot(ek[j]);
+        cnt += __popcll(bk);
+        at += __popcll(bk & lt);
       }
       uint32_t o = 0;
       if (lane == 0 && cnt > 0) o = atomicAdd(&s_add[turn], (uint32_t)cnt);
-      int at = base + (int)__shfl(o, 0, kWave);
+      at += (int)__shfl(o, 0, kWave);
 #pragma unroll
-      for (int j = 0; j < A; ++j) {
+      for (int j = A - 1; j >= 0; --j) {
         if (ek[j]) {
-          const int to = at + __popcll(bk[j] & lt);
-          s_node[to] = rk[j];
-          s_dist[to] = dk[j];
+          s_node[at] = rk[j];
+          s_dist[at] = dk[j];
+          ++at;
         }
-        at += __popcll(bk[j]);
       }
       __syncthreads();
       size = base + (int)s_add[turn];
@@ -915,7 +924,7 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
       if (tid == 0) {
         const uint32_t e = atomicAdd(huge.count, 1u);
         huge.q[e] = qi;
-        huge.bound[e] = __uint_as_float(s_bound);
+        huge.bound[e] = key_dist(s_bound);
       }
       continue;
     }
