@@ -290,9 +290,11 @@ abx_status abx_query_nearest_static(const abx_bvh *bvh, const float *points /*[m
  * (k > 64 is walked by one lane throughout.)
  * abx_set_nearest_budget sets the process-wide budget (<= 0: unlimited, i.e.
  * one lane per query throughout) and returns the previous one (INT64_MAX:
- * unlimited).  Default 8192.  With a limit, a batch of m queries uses
- * min(budget, 36 + k + min(m (10 + k) / 6400, 100 + 8 k) + m / 1024): small
- * batches leave the GPU idle and hand queries to whole workgroups sooner. */
+ * unlimited).  Default 22528.  With a limit, a batch of m queries uses
+ * min(budget, 36 + k + min(m (10 + k) / 6400, 100 + 8 k) + min(m / 1024,
+ * 8192)): small batches leave the GPU idle and hand queries to whole
+ * workgroups sooner.  On a tree of no more than m / 24 primitives only the
+ * first to reach the limit are handed over (one in 64, at least 8 per CU). */
 int64_t abx_set_nearest_budget(int64_t visits);
 
 /* -- traversal statistics ---------------------------------------------------

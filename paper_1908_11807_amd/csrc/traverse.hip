@@ -699,6 +699,19 @@ int device_cus() {
   return cus > 0 ? cus : 256;
 }
 
+// Queries of a batch that may leave their lanes: all of them, but on a tree of
+// no more than m / 24 primitives one in 64, or as many as the cooperative pass
+// answers at once.  Such a tree stands in the caches,
+// and a lane's visit to it costs less than a workgroup's; what pays there is to
+// take the few long walks out of their wavefronts (30 000 points on a shell,
+// 1e6 queries, k = 10: 0.5 % handed over, 1.8 ms against 12.7 with none).
+// Where they are many, all walks are long (equal points, where no node can be
+// skipped; 1e5 queries of k = 1 on 300 points: 265 us in their lanes, 1380 all
+// handed over, 290 this way; 1e6 on 10 000 points 27 ms, 52 and 26).
+uint32_t heavy_cap(int64_t n, int64_t m) {
+  return n <= m / 24 ? (uint32_t)std::max<int64_t>(m / 64, 8 * device_cus()) : UINT32_MAX;
+}
+
 template <int KIND, int FMT, int K>
 abx_status nearest_k(const abx_bvh *b, const float *pts, int64_t m, const int32_t *order, int k,
                      int32_t *idx, float *dist, int32_t *stats, const NearestScratch &ns,
@@ -706,7 +719,8 @@ abx_status nearest_k(const abx_bvh *b, const float *pts, int64_t m, const int32_
   const TreeArgs t = tree_args(b);
   const PlainMap map{k};
   const HeavyList heavy{ns.heavy_q, ns.heavy_bound, ns.counters,
-                        saves_walk(K) ? ns.heavy_state : nullptr, ns.state_cap};
+                        saves_walk(K) ? ns.heavy_state : nullptr, ns.state_cap,
+                        heavy_cap(b->n, m)};
   const unsigned g = grid_for(m, kNearestBlock);
   if (stats)
     return launch("nearest_stats", s, [&] {
@@ -777,12 +791,12 @@ abx_status nearest_fmt(const abx_bvh *b, const float *pts, int64_t m, const int3
 //   m / 1024   longer walks, as the one-lane pass fills the GPU for longer
 //              (1e7-point shell, k = 10: 1e6 queries 5.7 ms with 1200 to 1800
 //              visits, 9.3 with 8192; 1e7 queries 119 ms with 4096 to 12288,
-//              125 with 22528).
+//              125 with 22528: up to 8192).
 // A caller who asks for no limit (INT64_MAX) gets none.
 int64_t effective_budget(int64_t budget, int64_t m, int k) {
   if (budget == INT64_MAX) return budget;
   const int64_t usual = std::min<int64_t>(m * (10 + k) / 6400, 100 + 8 * k);
-  return std::min(budget, 36 + k + usual + m / 1024);
+  return std::min(budget, 36 + k + usual + std::min<int64_t>(m / 1024, 8192));
 }
 
 abx_status launch_nearest(const abx_bvh *b, const float *pts, int64_t m, const int32_t *order,

@@ -582,12 +582,14 @@ struct HeavyList {
   uint32_t *count = nullptr; // [0] entries, [1] next entry to serve
   int32_t *state = nullptr;  // saved walks, kHeavyStateWords words each (optional)
   uint32_t state_cap = 0;    // entries below this keep their walk
+  uint32_t cap = UINT32_MAX; // entries from here on are not taken: their lanes walk on
 };
 static_assert(kHeavyStateWords == 2 + 2 * kHeavyStateEntries + 2 * kMaxRegK, "saved walk layout");
 
 // Pass 1 for one query (one lane).  A walk that exceeds `budget` node
 // visits stops and hands the query to the cooperative pass with the k-th
-// distance it has found so far (an upper bound of the final one).
+// distance it has found so far (an upper bound of the final one), unless the
+// list is full: then it walks to its end.
 template <int KIND, int FMT, int K, bool STATS, int B, int W, class Map, typename DT>
 __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
                                              const float *__restrict__ pts, int64_t qi,
@@ -617,18 +619,26 @@ __device__ __forceinline__ void nearest_lane(const TreeArgs &t, const Map &map,
     int32_t node = info.root;
     const int64_t limit = budget < t.n ? budget : t.n;
     done = false;
-    for (int64_t it = 0; it < limit; ++it) {
-      if (STATS) ++visited;
-      node = knn_visit<KIND, FMT, K, B, kWin>(t, q, node, L, lds_n, lds_d, ovf_n,
-                                                     ovf_d, sp, nl, reads);
-      if (node < 0) node = knn_pop<B, kWin>(L.kth(), lds_n, lds_d, ovf_n, ovf_d, sp, nl);
-      if (node < 0) {
-        done = true;
-        break;
+    // (two loops, not one of two parts: that costs every walk of k = 1 5 %)
+    auto walk = [&](int64_t from, int64_t to) {
+      for (int64_t it = from; it < to; ++it) {
+        if (STATS) ++visited;
+        node = knn_visit<KIND, FMT, K, B, kWin>(t, q, node, L, lds_n, lds_d, ovf_n,
+                                                       ovf_d, sp, nl, reads);
+        if (node < 0) node = knn_pop<B, kWin>(L.kth(), lds_n, lds_d, ovf_n, ovf_d, sp, nl);
+        if (node < 0) {
+          done = true;
+          break;
+        }
       }
-    }
+    };
+    walk(0, limit);
+    uint32_t h = 0;
     if (!STATS && !done) {
-      const uint32_t h = atomicAdd(heavy.count, 1u);
+      h = atomicAdd(heavy.count, 1u);
+      if (h >= heavy.cap) walk(limit, t.n);
+    }
+    if (!STATS && !done && h < heavy.cap) {
       heavy.q[h] = (int32_t)qi;
       heavy.bound[h] = L.kth();
       // the walk so far: the next node (not yet visited), the unexplored
@@ -780,7 +790,7 @@ __global__ __launch_bounds__(T) void k_nearest_coop(
   __shared__ uint32_t s_add[3], s_found, s_h;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  const uint32_t total = heavy.count[0];
+  const uint32_t total = min(heavy.count[0], heavy.cap);
   // the first query by the workgroup's number (2048 empty workgroups that each
   // drew one took 17 us), the next ones as they come
   uint32_t h = blockIdx.x;
