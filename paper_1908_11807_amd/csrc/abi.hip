@@ -40,7 +40,7 @@ abx_status launch_wide(int kind, const NodeF32 *src, int64_t ni, const int32_t *
 // traverse.hip
 abx_status launch_query_codes(const abx_bvh *b, const float *q, int64_t m, int width,
                               uint32_t *codes, hipStream_t s, uint32_t *words,
-                              uint32_t mark = 0);
+                              uint32_t mark = 0, uint32_t *taken = nullptr);
 abx_status launch_spatial(const abx_bvh *b, int pred, const float *data, int64_t m,
                           const float *radii, float radius, const int32_t *order, int mode,
                           int32_t *counts, const int32_t *offsets, int32_t *indices, hipStream_t s,
@@ -91,17 +91,19 @@ abx_status row_offsets(int32_t *off, int64_t m, int32_t k, hipStream_t s) {
   });
 }
 
-// the state words of a spatial search, and the one-pass scheme's overflow flag
-__global__ void k_spatial_begin(uint32_t *words, uint32_t mark, uint32_t *flag) {
+// the state words of a spatial search, the counters of its kept rows' pool (if it
+// keeps any), and the one-pass scheme's overflow flag
+__global__ void k_spatial_begin(uint32_t *words, uint32_t mark, uint32_t *taken, uint32_t *flag) {
+  if (taken && threadIdx.x < kKeptParts) taken[threadIdx.x * kKeptCounter] = 0;
   if (threadIdx.x == 0) {
     words[0] = mark;
-    words[1] = words[2] = 0;
+    words[1] = 0;
     if (flag) flag[0] = 0;
   }
 }
 
-abx_status spatial_begin(uint32_t *words, uint32_t mark, uint32_t *flag, hipStream_t s) {
-  return launch("spatial_begin", s, [&] { k_spatial_begin<<<1, 64, 0, s>>>(words, mark, flag); });
+abx_status spatial_begin(uint32_t *words, uint32_t mark, uint32_t *taken, uint32_t *flag, hipStream_t s) {
+  return launch("spatial_begin", s, [&] { k_spatial_begin<<<1, kKeptParts, 0, s>>>(words, mark, taken, flag); });
 }
 
 // ---------------------------------------------------------------- build
@@ -281,11 +283,11 @@ uint32_t *spatial_words(char *sc, const QueryLayout &L) {
 // and the rows that the caller, a spatial search, is about to keep).
 abx_status order_queries(const abx_bvh *b, const float *data, int64_t m, int width, char *scratch,
                          const QueryLayout &L, const int32_t **order, hipStream_t s,
-                         uint32_t kept = 0) {
+                         uint32_t kept = 0, uint32_t *taken = nullptr) {
   uint32_t *codes = reinterpret_cast<uint32_t *>(scratch + L.codes);
   int32_t *ord = reinterpret_cast<int32_t *>(scratch + L.order);
   ABX_TRY(launch_query_codes(b, data, m, width, codes, s, spatial_words(scratch, L),
-                             kScratchTag | kScratchOrdered | kept));
+                             kScratchTag | kScratchOrdered | kept, taken));
   ABX_TRY(radix_sort(codes, nullptr, m, 30, scratch + L.sorted, ord, scratch + L.sort,
                      radix_sort_scratch_bytes(m, 30), s));
   ABX_TRY(order_guard(radix_sort_err_word(scratch + L.sort, m, 30), ord, m, s));
@@ -299,24 +301,53 @@ QueryLayout with_kept_rows(const QueryLayout &base, int64_t m, size_t scratch_by
   return scratch_bytes >= L.bytes ? L : base;
 }
 
-// (the code buffers of the query ordering are free once the order stands, the
-// heavy lists belong to nearest queries)
+// (the sorted codes are free once the order stands, the heavy lists belong to
+// nearest queries)
 KeptRows kept_rows(char *sc, const QueryLayout &L, int64_t m) {
   KeptRows k;
   k.buf = reinterpret_cast<int32_t *>(sc + L.rows);
-  k.more = reinterpret_cast<int32_t *>(sc + L.rows + kept_row_bytes(m));
-  k.pool = (int32_t)kept_pool(m);
+  char *at = sc + L.rows + kept_row_bytes(m);
+  k.more = reinterpret_cast<int32_t *>(at);
+  k.blocks = reinterpret_cast<int32_t *>(at += kept_pool_bytes(m));
+  k.taken = reinterpret_cast<uint32_t *>(at += kept_block_bytes(m));
+  k.parts = (int32_t)kept_parts(m);
+  k.part_blocks = (int32_t)kept_part_blocks(m);
   k.counts = reinterpret_cast<int32_t *>(sc + L.sorted);
   k.ext = reinterpret_cast<int32_t *>(sc + L.heavy_q);
-  k.long_list = reinterpret_cast<int32_t *>(sc + L.codes);
   k.words = spatial_words(sc, L);
   return k;
+}
+
+// Rows are kept if they are expected to find room: the keeping pass takes a
+// third to a half longer than a counting one over rows that fill their slots,
+// and if some of a batch's rows are walked again, that takes about as long as
+// filling all of them.  Measured, kept against counted and filled: 1e5 queries
+// on 1e6 evenly spread points, 9.9 hits a query 254 us (332), 23.5 288 (387),
+// 29.4 439 (408), 62 585 (516), 192 1002 (920); 1e6 queries 9.8 hits 495 us
+// (708), 23.5 680 (950), 39 1369 (1237); one query of 93 hits 163 (255), of 1000
+// 1350 (1210).  Where rows are uneven, it pays up to shorter means: 1e5 queries
+// in Gaussian clusters of 1e4 points, 14.9 hits 261 us (276), 19.3 345 (289).
+constexpr int64_t kKeptExpect = kKeptRow - kKeptRow / 4;  // by a caller's estimate, which leaves room
+
+// By the caller's estimate of all results, and by what a radius would find among
+// as many points spread evenly over the scene (where they are not, queries near
+// the points find more): seven tenths of the slots there are for a row.
+bool rows_short(const abx_bvh *b, const abx_predicates *p, int64_t capacity) {
+  if (capacity > kKeptExpect * p->m) return false;
+  if (p->kind != ABX_PRED_WITHIN || p->radii || !(p->radius > 0.0f)) return true;
+  double even = 0.5235987755982989 * (double)b->n;  // (a ball's share of its cube)
+  for (int a = 0; a < 3; ++a) {
+    const double side = (double)b->scene[3 + a] - b->scene[a], width = 2.0 * p->radius;
+    if (width < side) even *= width / side;
+  }
+  const double chunks = (double)(kept_part_blocks(p->m) * kept_parts(p->m) * kKeptBlock) / (double)p->m;
+  return even <= 0.7 * kKeptRow * (1.0 + std::min<double>(chunks, kKeptChunks));
 }
 
 // the total and state words of a finished count pass (blocks the host)
 struct SpatialState {
   int64_t total;
-  uint32_t mark, longer, extended, pad;
+  uint32_t mark, longer, pad[2];
 };
 abx_status read_spatial(const char *sc, const QueryLayout &L, SpatialState *st, hipStream_t s) {
   ABX_HIP(hipMemcpyAsync(st, sc + L.total, sizeof(*st), hipMemcpyDeviceToHost, s));
@@ -324,7 +355,9 @@ abx_status read_spatial(const char *sc, const QueryLayout &L, SpatialState *st, 
   return ABX_OK;
 }
 
-// The second pass: kept rows copied, longer ones walked again; without kept
+// The second pass: kept rows copied, the others walked again, in the order of
+// the first pass (neighbours share nodes; in a list by arrival, 64 of them a
+// wavefront, they walked slower than the whole batch does); without kept
 // rows every query walked again.  The rows lie in the order the first pass
 // walked in, so that pass's order counts (st.mark), not p->sort_queries.
 abx_status spatial_finish(const abx_bvh *bvh, const abx_predicates *p, char *sc, const QueryLayout &L,
@@ -338,11 +371,10 @@ abx_status spatial_finish(const abx_bvh *bvh, const abx_predicates *p, char *sc,
     return launch_spatial(bvh, p->kind, p->data, m, p->radii, p->radius, order, 1 /*fill*/, nullptr,
                           offsets, indices, s);
   const KeptRows kept = kept_rows(sc, L, m);
-  const int64_t longer = std::min<int64_t>(st.longer, m);
-  if (longer < m) ABX_TRY(launch_rows_copy(kept, m, order, offsets, indices, s));
-  if (longer == 0) return ABX_OK;
-  return launch_spatial(bvh, p->kind, p->data, longer, p->radii, p->radius, kept.long_list, 1 /*fill*/,
-                        nullptr, offsets, indices, s);
+  ABX_TRY(launch_rows_copy(kept, m, order, offsets, indices, s));
+  if (st.longer == 0) return ABX_OK;
+  return launch_spatial(bvh, p->kind, p->data, m, p->radii, p->radius, order, 1 /*fill*/, nullptr,
+                        offsets, indices, s, nullptr, &kept);
 }
 
 }  // namespace
@@ -693,18 +725,19 @@ abx_status abx_query_spatial(const abx_bvh *bvh, const abx_predicates *preds, vo
     return ABX_OK;
   }
   // The first pass keeps each row's first hits, in a scratch with room for them
-  // (a smaller one is walked twice), unless the caller expects most rows to be
-  // longer: a row that fits is copied, not walked for again.
+  // (a smaller one is walked twice), if they are expected to be short: a row that
+  // fits is copied, not walked for again.
   L = with_kept_rows(L, m, scratch_bytes);
-  const bool keep = L.keeps && capacity <= (kKeptRow - kKeptRow / 4) * m;
+  const bool keep = L.keeps && rows_short(bvh, preds, capacity);
   const uint32_t mark = keep ? kScratchKept : 0u;
   uint32_t *words = spatial_words(sc, L);
   const int32_t *order = nullptr;
-  if (preds->sort_queries)
-    ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s, mark));
-  else
-    ABX_TRY(spatial_begin(words, kScratchTag | mark, nullptr, s));
   const KeptRows kept = kept_rows(sc, L, m);
+  uint32_t *taken = keep ? kept.taken : nullptr;
+  if (preds->sort_queries)
+    ABX_TRY(order_queries(bvh, preds->data, m, width, sc, L, &order, s, mark, taken));
+  else
+    ABX_TRY(spatial_begin(words, kScratchTag | mark, taken, nullptr, s));
   ABX_TRY(launch_spatial(bvh, preds->kind, preds->data, m, preds->radii, preds->radius, order,
                          keep ? 4 /*keep*/ : 0 /*count*/, counts, nullptr, nullptr, s, nullptr,
                          keep ? &kept : nullptr));
@@ -769,7 +802,7 @@ abx_status abx_query_spatial_1p(const abx_bvh *bvh, const abx_predicates *preds,
   uint32_t *flag = reinterpret_cast<uint32_t *>(sc + L.bytes);
   int32_t *buf = reinterpret_cast<int32_t *>(sc + L.bytes + 256);
   const OnePass op{buf, buffer_size, flag, d_total, std::min<int64_t>(capacity, kMaxCount - 1)};
-  ABX_TRY(spatial_begin(spatial_words(sc, L), 0, flag, s));
+  ABX_TRY(spatial_begin(spatial_words(sc, L), 0, nullptr, flag, s));
   if (bvh->n == 0 || m == 0) {
     ABX_TRY(fill_u32(offsets, 0, (size_t)m + 1, s));
     ABX_TRY(fill_u32(d_total, 0, 2, s));

@@ -95,26 +95,59 @@ inline int64_t heavy_state_cap(int64_t m) {
 }
 
 // Rows kept by the first pass of a two-pass spatial query: kKeptRow slots for
-// every query (128 B) and, for the longer rows, extensions of kKeptMore slots
-// from a pool of one for every sixteen queries.  Rows beyond both, and batches
-// whose rows would take more than kKeptBytesMax, are walked twice.
+// every query (128 B) and, for the longer rows, up to kKeptChunks chunks of as
+// many slots, from a pool of six slots a query.  A wavefront takes chunks from
+// the pool by blocks of kKeptBlock, and the pool is in kKeptParts parts, each
+// with a counter of its own, which the wavefronts use in turn, so that dense
+// places draw on all of them: an atomic on one address takes some 50 ns (one
+// counter and an atomic for every longer row, 1e6 queries of 40 hits each: 5.9
+// ms, for every block of eight 2.5, as it is 1.37).  Longer rows, and those for
+// which the pool has run out, are walked again; batches whose rows would take
+// more than kKeptBytesMax are walked twice.
 constexpr int32_t kKeptRow = 32;
-constexpr int32_t kKeptMore = 96;
+constexpr int32_t kKeptChunks = 3;
+constexpr int32_t kKeptBlock = 8;
+constexpr int32_t kKeptParts = 64;
+constexpr int32_t kKeptCounter = 16;  // words between counters: a cache line each
+constexpr int32_t kKeptBlocks = kWave * kKeptChunks / kKeptBlock;  // of a wavefront, at most
 constexpr size_t kKeptBytesMax = size_t(8) << 30;
-inline int64_t kept_pool(int64_t m) { return m / 16 + 64; }
+// (a part for eight wavefronts at least: fewer of them need no more counters)
+inline int64_t kept_parts(int64_t m) {
+  const int64_t p = m / (8 * kWave) + 1;
+  return p < kKeptParts ? p : kKeptParts;
+}
+inline int64_t kept_part_blocks(int64_t m) {
+  const int64_t slots = kept_parts(m) * kKeptBlock * kKeptRow;
+  return (6 * m + slots - 1) / slots + kKeptParts / kept_parts(m);
+}
 inline size_t kept_row_bytes(int64_t m) { return (size_t)m * kKeptRow * 4; }
-inline size_t kept_bytes(int64_t m) { return kept_row_bytes(m) + (size_t)kept_pool(m) * kKeptMore * 4; }
+inline size_t kept_pool_bytes(int64_t m) {
+  return (size_t)(kept_part_blocks(m) * kept_parts(m)) * kKeptBlock * kKeptRow * 4;
+}
+inline size_t kept_block_bytes(int64_t m) {
+  return (size_t)((m + kWave - 1) / kWave) * kKeptBlocks * 4;
+}
+inline size_t kept_bytes(int64_t m) {
+  return kept_row_bytes(m) + kept_pool_bytes(m) + kept_block_bytes(m) + kKeptParts * kKeptCounter * 4;
+}
 
 // Rows the first pass of a two-pass spatial query keeps in the caller's
 // scratch, by sorted position of the query.
 struct KeptRows {
   int32_t *buf;        // [m * kKeptRow] each row's first hits
-  int32_t *more;       // [pool * kKeptMore] the next ones of longer rows
-  int32_t pool;
+  int32_t *more;       // the pool
+  int32_t *blocks;     // [wavefronts * kKeptBlocks] the blocks of it that each has taken
+  uint32_t *taken;     // [kKeptParts * kKeptCounter] blocks taken, or asked for in vain
+  int32_t parts, part_blocks;  // parts of the pool, blocks of a part
   int32_t *counts;     // [m] hits
-  int32_t *ext;        // [m] rows of more than kKeptRow hits: extension, or -1
-  int32_t *long_list;  // queries whose rows were not kept whole, words[1] of them
-  uint32_t *words;     // [0]: what stands in this scratch (kScratch...); [2]: extensions asked for
+  int32_t *ext;        // [m] rows of more than kKeptRow hits: their chunks, a byte each (from
+                       // the lowest) that numbers them among the wavefront's; -1: not kept whole
+  uint32_t *words;     // [0]: what stands in this scratch (kScratch...); [1]: 1 if a row was not
+                       // kept whole
+  __device__ bool whole(int64_t tq) const { return counts[tq] <= kKeptRow || ext[tq] >= 0; }
+  __device__ int32_t *chunk(int32_t block, int32_t e) const {
+    return more + ((int64_t)block * kKeptBlock + e % kKeptBlock) * kKeptRow;
+  }
 };
 
 // Word [0]: what the last search of queries left in the scratch, for the fill

@@ -49,16 +49,26 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
                                                         int32_t *__restrict__ out_counts,
                                                         const int32_t *__restrict__ offsets,
                                                         int32_t *__restrict__ indices) {
-  // passes that write hits: half the window, the other half holds them
-  constexpr bool kHolds = MODE == MODE_KEEP || MODE == MODE_STORE || MODE == MODE_FILL;
+  // passes that hold hits: half the window, the other half holds them
+  constexpr bool kHolds = MODE == MODE_KEEP || MODE == MODE_STORE;
   constexpr int kWin = kHolds ? kLdsDepthSpatial / 2 : kLdsDepthSpatial;
   __shared__ int32_t s_stack[kWin * kSpatialBlock];
   __shared__ int32_t s_held[kHolds ? 8 * kSpatialBlock : 1];
+  // keeping pass: chunks that the wavefront's rows have asked for, its blocks
+  __shared__ int32_t s_taken, s_block[MODE == MODE_KEEP ? kKeptBlocks : 1];
+  static_assert(kSpatialBlock == kWave, "a workgroup's chunks are one wavefront's");
+  static_assert(kKeptChunks < 4 && kWave * kKeptChunks < 256, "three bytes number a row's chunks");
+  if (MODE == MODE_KEEP) {
+    s_taken = 0;
+    if (threadIdx.x < kKeptBlocks) s_block[threadIdx.x] = 0;
+  }
   const int64_t tq = xcd_tile(blockIdx.x, gridDim.x) * kSpatialBlock + threadIdx.x;
   if (tq >= qa.m) return;
   // the fill pass of the one-pass scheme runs only after an overflow, and
   // only when the caller's index buffer holds every hit
   if (MODE == MODE_FILL && qa.flag && (qa.flag[0] == 0 || *qa.total > qa.capacity)) return;
+  // after a keeping pass only the rows that it did not keep whole are filled
+  if (MODE == MODE_FILL && qa.kept.counts && qa.kept.whole(tq)) return;
   const int64_t qi = qa.order ? qa.order[tq] : tq;
   SpatialQuery<PRED> q;
   if (PRED == ABX_PRED_WITHIN) {
@@ -90,20 +100,41 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
   // that the kept rows make unnecessary took 404.  The storing pass of the
   // one-pass search, 32 slots a row: 294 -> 270 us.)
   ABX_LDS int32_t *held = (ABX_LDS int32_t *)(s_held) + threadIdx.x;
-  int32_t ext = -1;
+  bool keeps = MODE == MODE_KEEP;  // the row so far is kept whole
+  int32_t ext = 0;                 // its chunks
+  int32_t *room = MODE == MODE_KEEP ? qa.kept.buf + tq * kKeptRow : nullptr;
+  auto load_block = [&](int32_t b) {
+    return __hip_atomic_load(&s_block[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
   auto keep = [&](int32_t at) {  // hits at .. at + 7 of the row
-    int32_t *to = nullptr;
-    if (at < kKeptRow) {
-      to = qa.kept.buf + tq * kKeptRow + at;
-    } else if (at < kKeptRow + kKeptMore) {
-      if (at == kKeptRow) {
-        const uint32_t e = atomicAdd(qa.kept.words + 2, 1u);
-        ext = e < (uint32_t)qa.kept.pool ? (int32_t)e : -1;
+    const int32_t c = at / kKeptRow - 1, in = at % kKeptRow;
+    if (in == 0 && at > 0) {
+      keeps = c < kKeptChunks;
+      if (!keeps) return;
+      // the wavefront's chunks, numbered as its lanes ask for them; who opens a
+      // block of them takes it from the pool, unless that had run out before
+      const int32_t e = atomicAdd(&s_taken, 1), b = e / kKeptBlock;
+      if (e % kKeptBlock == 0) {
+        int32_t block = -1;
+        if (b == 0 || load_block(b - 1) >= 0) {
+          const int32_t wave = (int32_t)(tq / kWave), part = wave % qa.kept.parts;
+          const uint32_t f = atomicAdd(qa.kept.taken + part * kKeptCounter, 1u);
+          if (f < (uint32_t)qa.kept.part_blocks) {
+            block = part * qa.kept.part_blocks + (int32_t)f;
+            qa.kept.blocks[(int64_t)wave * kKeptBlocks + b] = block;
+          }
+        }
+        __hip_atomic_store(&s_block[b], block, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
-      if (ext >= 0) to = qa.kept.more + (int64_t)ext * kKeptMore + (at - kKeptRow);
+      // (a wavefront runs as one: the block is stored before any lane reads it)
+      __builtin_amdgcn_wave_barrier();
+      const int32_t block = load_block(b);
+      keeps = block >= 0;
+      if (!keeps) return;
+      ext |= e << (8 * c);
+      room = qa.kept.chunk(block, e);
     }
-    if (!to) return;
-    int4 *t4 = reinterpret_cast<int4 *>(to);
+    int4 *t4 = reinterpret_cast<int4 *>(room + in);
     t4[0] = make_int4(held[0], held[kSpatialBlock], held[2 * kSpatialBlock], held[3 * kSpatialBlock]);
     t4[1] = make_int4(held[4 * kSpatialBlock], held[5 * kSpatialBlock], held[6 * kSpatialBlock], held[7 * kSpatialBlock]);
   };
@@ -130,11 +161,12 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
       if (MODE == MODE_STATS) ++leaf_reads;
       if (!q.test(b)) return;
     }
-    if (kHolds) held[(cnt & 7) * kSpatialBlock] = idx;
+    if (MODE == MODE_FILL && cnt < row_len) out[cnt] = idx;
+    if (MODE == MODE_STORE || keeps) held[(cnt & 7) * kSpatialBlock] = idx;
     ++cnt;
     if (kHolds && (cnt & 7) == 0) {
-      if (MODE == MODE_KEEP) keep(cnt - 8);
-      else put(cnt - 8);
+      if (MODE == MODE_STORE) put(cnt - 8);
+      else if (keeps) keep(cnt - 8);
     }
   };
 
@@ -192,14 +224,13 @@ __global__ __launch_bounds__(kSpatialBlock) void k_spatial(TreeArgs t, QueryArgs
     }
   }
   if (MODE == MODE_COUNT || MODE == MODE_STORE || MODE == MODE_KEEP) out_counts[qi] = cnt;
-  if ((MODE == MODE_STORE || MODE == MODE_FILL) && (cnt & 7)) put(cnt & ~7);
+  if (MODE == MODE_STORE && (cnt & 7)) put(cnt & ~7);
   if (MODE == MODE_KEEP) {
-    if (cnt & 7) keep(cnt & ~7);
+    if (keeps && (cnt & 7)) keep(cnt & ~7);
     qa.kept.counts[tq] = cnt;
     if (cnt > kKeptRow) {
-      if (cnt > kKeptRow + kKeptMore) ext = -1;
-      qa.kept.ext[tq] = ext;
-      if (ext < 0) qa.kept.long_list[atomicAdd(qa.kept.words + 1, 1u)] = (int32_t)qi;
+      qa.kept.ext[tq] = keeps ? ext : -1;
+      if (!keeps && qa.kept.words[1] == 0) qa.kept.words[1] = 1;
     }
   }
   if (MODE == MODE_STORE && cnt > qa.bufsize) atomicOr(qa.flag, 1u);
@@ -458,16 +489,18 @@ __device__ __forceinline__ uint32_t spread10q(uint32_t x) {
   return x;
 }
 
-// `words`: the spatial search's state words, set to (mark, 0, 0).
+// `words`: the spatial search's state words, set to (mark, 0); `taken`: the
+// counters of its kept rows' pool (null: it keeps none).
 template <int W>
 __global__ __launch_bounds__(kTravBlock) void k_query_codes(const float *__restrict__ q, int64_t m,
                                                             TreeArgs t, uint32_t *__restrict__ codes,
                                                             uint32_t *__restrict__ words,
-                                                            uint32_t mark) {
+                                                            uint32_t mark, uint32_t *__restrict__ taken) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (taken && i < kKeptParts) taken[i * kKeptCounter] = 0;
   if (i == 0) {
     words[0] = mark;
-    words[1] = words[2] = 0;
+    words[1] = 0;
   }
   if (i >= m) return;
   uint32_t c[3];
@@ -505,13 +538,14 @@ TreeArgs tree_args(const abx_bvh *b) {
 }
 
 abx_status launch_query_codes(const abx_bvh *b, const float *q, int64_t m, int width,
-                              uint32_t *codes, hipStream_t s, uint32_t *words, uint32_t mark) {
+                              uint32_t *codes, hipStream_t s, uint32_t *words, uint32_t mark,
+                              uint32_t *taken) {
   if (m == 0) return ABX_OK;
   const TreeArgs t = tree_args(b);
   const unsigned g = grid_for(m, kTravBlock);
   if (width == 3)
-    return launch("query_codes", s, [&] { k_query_codes<3><<<g, kTravBlock, 0, s>>>(q, m, t, codes, words, mark); });
-  return launch("query_codes", s, [&] { k_query_codes<6><<<g, kTravBlock, 0, s>>>(q, m, t, codes, words, mark); });
+    return launch("query_codes", s, [&] { k_query_codes<3><<<g, kTravBlock, 0, s>>>(q, m, t, codes, words, mark, taken); });
+  return launch("query_codes", s, [&] { k_query_codes<6><<<g, kTravBlock, 0, s>>>(q, m, t, codes, words, mark, taken); });
 }
 
 template <int KIND, int PRED, int FMT>
@@ -553,7 +587,7 @@ abx_status launch_spatial(const abx_bvh *b, int pred, const float *data, int64_t
                           int32_t *counts, const int32_t *offsets, int32_t *indices, hipStream_t s,
                           const OnePass *op, const KeptRows *kept) {
   if (m == 0) return ABX_OK;
-  QueryArgs qa{};
+  QueryArgs qa{};  // (no kept rows, no one-pass state)
   qa.data = data;
   qa.m = m;
   qa.radii = radii;
@@ -611,8 +645,8 @@ __global__ __launch_bounds__(kTravBlock) void k_spatial_compact(const int32_t *_
 // The second pass of the two-pass scheme when the first one kept the rows
 // (radius search, 1e6 queries of ten hits: 922 -> 600 us a call; box overlaps
 // of 1e6 boxes, build included, 1490 -> 1150 us): each is copied to its place
-// (those not kept whole are walked again, from the list the first pass made).  Eight lanes a row read 16 B each, neighbouring
-// rows one after another; the counts tell an empty row without touching its
+// (those not kept whole are walked again).  Eight lanes a row read 16 B each,
+// neighbouring rows one after another; the counts tell an empty row without touching its
 // slots.  No more is written of a row than its offsets give it.
 __global__ __launch_bounds__(kTravBlock) void k_rows_copy(KeptRows kept, int64_t m,
                                                           const int32_t *__restrict__ order,
@@ -625,7 +659,7 @@ __global__ __launch_bounds__(kTravBlock) void k_rows_copy(KeptRows kept, int64_t
   if (tq >= m) return;
   const int32_t hits = kept.counts[tq];
   if (4 * l >= hits) return;
-  int32_t ext = -1;
+  int32_t ext = 0;
   if (hits > kKeptRow) {
     ext = kept.ext[tq];
     if (ext < 0) return;
@@ -643,7 +677,10 @@ __global__ __launch_bounds__(kTravBlock) void k_rows_copy(KeptRows kept, int64_t
     if (e + 3 < c) out[e + 3] = v.w;
     e += kKeptRow;
     if (e >= c) break;
-    from = reinterpret_cast<const int4 *>(kept.more + (int64_t)ext * kKeptMore + (e - 4 * l - kKeptRow));
+    const int32_t n = ext & 255;
+    from = reinterpret_cast<const int4 *>(
+        kept.chunk(kept.blocks[tq / kWave * kKeptBlocks + n / kKeptBlock], n));
+    ext >>= 8;
   }
 }
 

@@ -70,7 +70,7 @@ struct QueryArgs {
   const float *radii;
   float radius;
   const int32_t *order;  // sorted position -> caller's query index (or null)
-  KeptRows kept;         // keeping pass only
+  KeptRows kept;         // keeping pass, and the fill after it
   // one-pass (1P) scheme only
   int32_t *buf;          // [m * bufsize] stored hits, one row per sorted position
   int32_t bufsize;
