@@ -24,7 +24,8 @@
 namespace abx {
 
 constexpr int kForestBlock = 256;
-constexpr int kForestChunk = 16384;  // consecutive points per workgroup in the box reduction
+// consecutive points per workgroup in the box reduction
+constexpr int kForestChunkMin = 256, kForestChunkMax = 16384;
 constexpr int kForestMaxTrees = 512;
 constexpr int kForestKeyShift = 54;
 constexpr int kForestBits = 18;
@@ -67,14 +68,16 @@ __global__ void k_forest_box_init(int32_t *tbox, int T, TreeHeader *hdr) {
 // whole workgroup, the trees of another chunk by a wavefront each, so a box
 // costs one atomic per bound: the boxes of all the trees lie in a few cache
 // lines, where atomics queue.  64 sets, 9.6e6 points in all: 854 us with a run
-// of 256 consecutive points a thread, 74 us this way.
+// of 256 consecutive points a thread, 74 us this way.  Fewer points are cut into
+// a chunk for each CU, or small trees would all fall to a few workgroups (512
+// sets of 3 to 30 points: 596 us in one chunk, 69 this way; 64 of 10 to 2000 points 52, 13.5).
 __global__ __launch_bounds__(kForestBlock) void k_forest_boxes(const float *__restrict__ p, int64_t N,
                                                                const int64_t *__restrict__ off, int T,
-                                                               int32_t *tbox, TreeHeader *hdr) {
+                                                               int chunk, int32_t *tbox, TreeHeader *hdr) {
   constexpr int kWaves = kForestBlock / kWave;
   __shared__ float s[kWaves][6];
-  const int64_t c0 = (int64_t)blockIdx.x * kForestChunk;
-  const int64_t c1 = c0 + kForestChunk < N ? c0 + kForestChunk : N;
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  const int64_t c1 = c0 + chunk < N ? c0 + chunk : N;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   float lo[3], hi[3];
   int bad = 0;
@@ -376,11 +379,12 @@ abx_status forest_launch_build(const float *pts, int64_t N, const int64_t *off_d
   ABX_TRY(launch("forest_box_init", s, [&] {
     k_forest_box_init<<<grid_for(T, 256), 256, 0, s>>>(tbox, T, hdr);
   }));
-  if (N > 0)
+  if (N > 0) {
+    const int chunk = (int)std::clamp<int64_t>(N / device_cus(), kForestChunkMin, kForestChunkMax);
     ABX_TRY(launch("forest_boxes", s, [&] {
-      k_forest_boxes<<<grid_for(N, kForestChunk), kForestBlock, 0, s>>>(
-          pts, N, off_dev, T, tbox, hdr);
+      k_forest_boxes<<<grid_for(N, chunk), kForestBlock, 0, s>>>(pts, N, off_dev, T, chunk, tbox, hdr);
     }));
+  }
   ABX_TRY(launch("forest_boxes_final", s, [&] {
     k_forest_boxes_final<<<1, kForestMaxTrees, 0, s>>>(tbox, T, off_dev, tscene, off_copy, hdr);
   }));
