@@ -189,7 +189,13 @@ abx_status abx_bvh_destroy(abx_bvh *bvh);
 abx_status abx_bvh_get_layout(const abx_bvh *bvh, abx_bvh_layout *out /*host*/);
 
 /* -- spatial queries (section 2.2 spatial traversal, 2P count-and-fill) ---
- * abx_query_spatial_sizes: scratch bytes for a batch of m predicates.
+ * abx_query_spatial_sizes: scratch bytes for a batch of m predicates, with the
+ *   room to keep rows where the search would (about 154 bytes a query, up to 8
+ *   GiB in all; they double what a search of small results takes).
+ * abx_query_spatial_sizes_for: the same for a search with this capacity, and
+ *   the least bytes that abx_query_spatial and the other calls on these
+ *   predicates accept (abx_query_spatial_stats never uses more).  Either may be
+ *   NULL.
  * abx_query_spatial: orders the queries (optional), counts the hits of each
  *   query by a stack traversal, scans the counts into offsets[0..m] (rows in
  *   the caller's query order, offsets[0] = 0, offsets[m] = total), and
@@ -209,6 +215,9 @@ abx_status abx_bvh_get_layout(const abx_bvh *bvh, abx_bvh_layout *out /*host*/);
  *   abx_query_spatial on the same predicates and scratch. */
 abx_status abx_query_spatial_sizes(const abx_bvh *bvh, const abx_predicates *preds,
                                    size_t *scratch_bytes /*host*/);
+abx_status abx_query_spatial_sizes_for(const abx_bvh *bvh, const abx_predicates *preds,
+                                       int64_t capacity, size_t *least_bytes /*host*/,
+                                       size_t *scratch_bytes /*host*/);
 abx_status abx_query_spatial(const abx_bvh *bvh, const abx_predicates *preds, void *scratch,
                              size_t scratch_bytes, int32_t *offsets /*[m+1]*/, int32_t *indices,
                              int64_t capacity, int64_t *total /*host*/, abx_stream_t stream);
@@ -218,7 +227,7 @@ abx_status abx_query_spatial_fill(const abx_bvh *bvh, const abx_predicates *pred
 
 /* -- spatial queries, one pass (section 2.2, the 1P scheme) ---------------
  * abx_query_spatial_1p_sizes: scratch bytes for m predicates with a per-query
- *   estimate buffer_size (1 .. 65536) of the hits: the 2P scratch plus
+ *   estimate buffer_size (1 .. 65536) of the hits: the least 2P scratch plus
  *   m * buffer_size int32 slots.
  * abx_query_spatial_1p: orders the queries (optional), then ONE traversal
  *   counts every query's hits and stores the first buffer_size of them in

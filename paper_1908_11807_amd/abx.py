@@ -139,6 +139,7 @@ def _lib():
             "abx_bvh_destroy": [vp],
             "abx_bvh_get_layout": [vp, P(Layout)],
             "abx_query_spatial_sizes": [vp, P(Predicates), P(sz)],
+            "abx_query_spatial_sizes_for": [vp, P(Predicates), i64, P(sz), P(sz)],
             "abx_query_spatial": [vp, P(Predicates), vp, sz, vp, vp, i64, P(i64), vp],
             "abx_query_spatial_fill": [vp, P(Predicates), vp, sz, vp, vp, i64, vp],
             "abx_query_spatial_1p_sizes": [vp, P(Predicates), i32, P(sz)],
@@ -332,22 +333,32 @@ def query_spatial(bvh, data, radius=None, radii=None, predicate="within", sort_q
     L = _lib()
     pr, d, rr = _preds(data, predicate, radius, radii, sort_queries)
     m = d.shape[0]
-    sb = C.c_size_t()
-    _check(L.abx_query_spatial_sizes(bvh.handle, C.byref(pr), C.byref(sb)), "abx_query_spatial_sizes")
-    scratch = _bytes(sb.value, d.device)
-    offsets = torch.empty(m + 1, dtype=torch.int32, device=d.device)
     cap = int(capacity or 0)
-    indices = torch.empty(max(cap, 1), dtype=torch.int32, device=d.device)
-    total = C.c_int64()
-    st = L.abx_query_spatial(bvh.handle, C.byref(pr), _ptr(scratch), sb.value, _ptr(offsets),
-                             _ptr(indices) if cap > 0 else C.c_void_p(0), cap, C.byref(total),
-                             _stream())
-    if st == ERR_CAPACITY:
-        indices = torch.empty(max(total.value, 1), dtype=torch.int32, device=d.device)
-        st = L.abx_query_spatial_fill(bvh.handle, C.byref(pr), _ptr(scratch), sb.value,
-                                      _ptr(offsets), _ptr(indices), total.value, _stream())
-    _check(st, "abx_query_spatial")
-    return offsets, indices[: total.value]
+    least, sb = C.c_size_t(), C.c_size_t()
+    _check(L.abx_query_spatial_sizes_for(bvh.handle, C.byref(pr), cap, C.byref(least), C.byref(sb)),
+           "abx_query_spatial_sizes_for")
+
+    def search(scratch_bytes):
+        scratch = _bytes(scratch_bytes, d.device)
+        offsets = torch.empty(m + 1, dtype=torch.int32, device=d.device)
+        indices = torch.empty(max(cap, 1), dtype=torch.int32, device=d.device)
+        total = C.c_int64()
+        st = L.abx_query_spatial(bvh.handle, C.byref(pr), _ptr(scratch), scratch_bytes,
+                                 _ptr(offsets), _ptr(indices) if cap > 0 else C.c_void_p(0), cap,
+                                 C.byref(total), _stream())
+        if st == ERR_CAPACITY:
+            indices = torch.empty(max(total.value, 1), dtype=torch.int32, device=d.device)
+            st = L.abx_query_spatial_fill(bvh.handle, C.byref(pr), _ptr(scratch), scratch_bytes,
+                                          _ptr(offsets), _ptr(indices), total.value, _stream())
+        _check(st, "abx_query_spatial")
+        return offsets, indices[: total.value]
+
+    if sb.value > least.value:
+        try:
+            return search(sb.value)
+        except torch.OutOfMemoryError:
+            pass    # no room to keep rows: the search walks twice
+    return search(least.value)
 
 
 def query_spatial_1p(bvh, data, buffer_size, radius=None, radii=None, predicate="within",
@@ -434,7 +445,8 @@ def query_spatial_stats(bvh, data, radius=None, radii=None, predicate="within", 
     L = _lib()
     pr, d, rr = _preds(data, predicate, radius, radii, sort_queries)
     sb = C.c_size_t()
-    _check(L.abx_query_spatial_sizes(bvh.handle, C.byref(pr), C.byref(sb)), "abx_query_spatial_sizes")
+    _check(L.abx_query_spatial_sizes_for(bvh.handle, C.byref(pr), 0, C.byref(sb), None),
+           "abx_query_spatial_sizes_for")
     scratch = _bytes(sb.value, d.device)
     stats = torch.empty((d.shape[0], 2), dtype=torch.int32, device=d.device)
     _check(L.abx_query_spatial_stats(bvh.handle, C.byref(pr), _ptr(scratch), sb.value, _ptr(stats),

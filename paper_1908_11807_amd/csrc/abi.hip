@@ -333,6 +333,7 @@ constexpr int64_t kKeptExpect = kKeptRow - kKeptRow / 4;  // by a caller's estim
 // as many points spread evenly over the scene (where they are not, queries near
 // the points find more): seven tenths of the slots there are for a row.
 bool rows_short(const abx_bvh *b, const abx_predicates *p, int64_t capacity) {
+  if (b->n == 0 || p->m == 0) return false;
   if (capacity > kKeptExpect * p->m) return false;
   if (p->kind != ABX_PRED_WITHIN || p->radii || !(p->radius > 0.0f)) return true;
   double even = 0.5235987755982989 * (double)b->n;  // (a ball's share of its cube)
@@ -693,7 +694,18 @@ abx_status abx_query_spatial_sizes(const abx_bvh *bvh, const abx_predicates *pre
   ABX_TRY(check_bvh(bvh));
   ABX_TRY(check_preds(preds));
   if (!scratch_bytes) return ABX_ERR_INVALID_ARG;
-  *scratch_bytes = query_layout(preds->m, false, true).bytes;
+  return abx_query_spatial_sizes_for(bvh, preds, 0, nullptr, scratch_bytes);
+}
+
+abx_status abx_query_spatial_sizes_for(const abx_bvh *bvh, const abx_predicates *preds,
+                                       int64_t capacity, size_t *least_bytes,
+                                       size_t *scratch_bytes) {
+  ABX_TRY(check_bvh(bvh));
+  ABX_TRY(check_preds(preds));
+  if (capacity < 0) return ABX_ERR_INVALID_ARG;
+  if (least_bytes) *least_bytes = query_layout(preds->m).bytes;
+  if (scratch_bytes)
+    *scratch_bytes = query_layout(preds->m, false, rows_short(bvh, preds, capacity)).bytes;
   return ABX_OK;
 }
 
