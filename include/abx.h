@@ -326,8 +326,9 @@ abx_status abx_query_nearest_stats(const abx_bvh *bvh, const float *points, int6
  *   x as the most significant bit of each triple (section 2.1).
  * abx_radix_sort_pairs: stable LSD radix sort of n (key, value) pairs on the
  *   low `key_bits` bits (keys uint32 when key_bits <= 32, else uint64;
- *   values int32, or the identity 0..n-1 when vals_in is NULL).  Each pass
- *   is one launch in which a tile of keys waits for the digit counts of the
+ *   values int32, or the identity 0..n-1 when vals_in is NULL).  Up to 12 288
+ *   pairs are sorted by one workgroup in one launch.  Of more, each pass is
+ *   one launch in which a tile of keys waits for the digit counts of the
  *   tiles before it (section 2.1 "Sort the bounding boxes").  That wait is
  *   bounded: a tile that gives up records it in the scratch buffer and the
  *   sort completes with an invalid (though in-bounds) output.

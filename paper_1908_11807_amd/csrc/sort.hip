@@ -328,10 +328,8 @@ constexpr int kSmallThreads = 1024;
 constexpr int64_t kSmallMax = 12 * kSmallThreads;
 
 template <typename K, int kItems>
-__global__ __launch_bounds__(kSmallThreads) void k_sort_small(const K *__restrict__ kin,
-                                                              const int32_t *__restrict__ vin,
-                                                              K *__restrict__ kout,
-                                                              int32_t *__restrict__ vout, int n,
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(const K *kin, const int32_t *vin, K *kout,
+                                                              int32_t *vout, int n,
                                                               int key_bits) {
   constexpr int kT = kSmallThreads, kW = kT / kWave;
   __shared__ uint32_t s_cnt[kW][kRadix];
@@ -395,12 +393,22 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const K *__restric
       }
     }
   }
+  // every value is read before anything is stored, so that the outputs may take
+  // the inputs' memory in any other way than the refused ones (keys over the
+  // values, say), as in a sort of several passes
+  int32_t v[kItems];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const int i = base + r * kWave;
+    v[r] = i < n && vin ? vin[from[r]] : (int32_t)from[r];
+  }
+  __syncthreads();
 #pragma unroll
   for (int r = 0; r < kItems; ++r) {
     const int i = base + r * kWave;
     if (i < n) {
       kout[i] = k[r];
-      vout[i] = vin ? vin[from[r]] : (int32_t)from[r];
+      vout[i] = v[r];
     }
   }
 }
