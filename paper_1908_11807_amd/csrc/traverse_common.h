@@ -326,12 +326,6 @@ struct KnnList {
     }
   }
   __device__ __forceinline__ void offer(float d, int32_t idx) { offer_key(knn_key(d, idx)); }
-  // drop the front entry (sentinel or taken), pad the back with an empty slot
-  __device__ __forceinline__ void shift() {
-#pragma unroll
-    for (int j = 0; j + 1 < K; ++j) key[j] = key[j + 1];
-    key[K - 1] = kKeyEmpty;
-  }
 };
 
 struct KnnQuery {

@@ -81,3 +81,71 @@ def test_rows_end_where_their_offsets_do(setup):
                                for o, c in zip(off.cpu().numpy(), short)])
         assert np.array_equal(got[:len(want)], want)
         assert (got[len(want):] == -7).all()      # nothing beyond the last row
+
+
+def one_pass(t, q, scratch, sort, buffer, radius):
+    """The one-pass search with room for one result: offsets and total."""
+    pr = abx.Predicates(abx.PRED_WITHIN, q.data_ptr(), M, None, radius, sort)
+    off = torch.empty(M + 1, dtype=torch.int32, device="cuda")
+    idx = torch.empty(1, dtype=torch.int32, device="cuda")
+    info = torch.zeros(2, dtype=torch.int32, device="cuda")
+    assert abx.library().abx_query_spatial_1p(t.handle, C.byref(pr), buffer, VP(scratch.data_ptr()),
+                                              scratch.numel(), VP(off.data_ptr()),
+                                              VP(idx.data_ptr()), 1, VP(info.data_ptr()),
+                                              stream()) == abx.OK
+    assert int(info[0]) == abx.ERR_CAPACITY
+    return off, int(off[-1])
+
+
+@pytest.mark.parametrize("sort", [0, 1])
+def test_a_search_voids_the_rows_kept_before_it(setup, sort):
+    # one scratch, large enough for kept rows throughout: what an earlier search
+    # kept there must not be filled after a search that keeps none
+    t, q, off, idx = setup
+    other = torch.from_numpy(datagen.uniform_cube(M, 9)).cuda()
+    smaller = 0.6 * RADIUS
+    want = abx.query_spatial(t, other, radius=smaller, capacity=N * M // 4)
+    b = C.c_size_t()
+    pr = abx.Predicates(abx.PRED_WITHIN, q.data_ptr(), M, None, RADIUS, 1)
+    assert abx.library().abx_query_spatial_1p_sizes(t.handle, C.byref(pr), 64, C.byref(b)) == abx.OK
+    sc = scratch_for(t, q)
+    sc = torch.full((max(sc.numel(), b.value),), 0x5a, dtype=torch.uint8, device="cuda")
+
+    def kept_rows():
+        got, total = count(t, q, sc, 1)
+        assert torch.equal(got, off)
+        return total
+
+    # the rows kept are there: filled after it, without and after other calls'
+    # work on the same predicates
+    total = kept_rows()
+    assert torch.equal(fill(t, q, sc, 1, off, total), idx)
+    # a one-pass search in the same scratch
+    kept_rows()
+    o, n = one_pass(t, other, sc, sort, 64, smaller)
+    assert torch.equal(o, want[0])
+    assert torch.equal(fill(t, other, sc, sort, o, n, smaller), want[1])
+    # a two-pass search that keeps none: the caller expects long rows
+    kept_rows()
+    pr = abx.Predicates(abx.PRED_WITHIN, other.data_ptr(), M, None, smaller, sort)
+    room = 24 * M + 1
+    some = torch.empty(max(room, n), dtype=torch.int32, device="cuda")
+    o = torch.empty(M + 1, dtype=torch.int32, device="cuda")
+    tot = C.c_int64()
+    st = abx.library().abx_query_spatial(t.handle, C.byref(pr), VP(sc.data_ptr()), sc.numel(),
+                                         VP(o.data_ptr()), VP(some.data_ptr()), max(room, n),
+                                         C.byref(tot), stream())
+    assert st == abx.OK and tot.value == n and torch.equal(some[:n], want[1])
+    assert torch.equal(fill(t, other, sc, sort, o, n, smaller), want[1])
+
+
+@pytest.mark.parametrize("sort", [False, True])
+def test_rows_walked_again_with_radii_of_their_own(setup, sort):
+    t, q, _, _ = setup
+    rng = np.random.default_rng(3)
+    radii = torch.from_numpy(rng.uniform(0.0, 0.35, M).astype(np.float32)).cuda()
+    want = abx.query_spatial(t, q, radii=radii, sort_queries=sort, capacity=N * M // 2)
+    rows = np.diff(want[0].cpu().numpy())
+    assert (rows > 128).sum() > 50 and ((rows > 32) & (rows <= 128)).sum() > 50
+    got = abx.query_spatial(t, q, radii=radii, sort_queries=sort)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
