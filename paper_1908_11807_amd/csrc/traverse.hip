@@ -829,11 +829,13 @@ abx_status nearest_fmt(const abx_bvh *b, const float *pts, int64_t m, const int3
 //              (1e7-point shell, k = 10: 1e6 queries 5.7 ms with 1200 to 1800
 //              visits, 9.3 with 8192; 1e7 queries 119 ms with 4096 to 12288,
 //              125 with 22528: up to 8192).
+// A 4-wide walk makes about half as many visits, so its upper limits are half.
 // A caller who asks for no limit (INT64_MAX) gets none.
-int64_t effective_budget(int64_t budget, int64_t m, int k) {
+int64_t effective_budget(int64_t budget, int64_t m, int k, bool wide) {
   if (budget == INT64_MAX) return budget;
+  if (wide) budget = std::max<int64_t>(1, budget / 2);
   const int64_t usual = std::min<int64_t>(m * (10 + k) / 6400, 100 + 8 * k);
-  return std::min(budget, 36 + k + usual + std::min<int64_t>(m / 1024, 8192));
+  return std::min(budget, 36 + k + usual + std::min<int64_t>(m / 1024, wide ? 4096 : 8192));
 }
 
 abx_status launch_nearest(const abx_bvh *b, const float *pts, int64_t m, const int32_t *order,
@@ -855,10 +857,8 @@ abx_status launch_nearest(const abx_bvh *b, const float *pts, int64_t m, const i
     ABX_BY_FORMAT(ABX_HEAP, ABX_PRIM_BOXES);
 #undef ABX_HEAP
   }
-  // a 4-wide walk makes about half as many node visits as a binary one
-  const int64_t b_eff = b->format == ABX_NODES_Q16W && budget != INT64_MAX
-                            ? std::max<int64_t>(1, budget / 2) : budget;
-  const NearestScratch ns{heavy_q, heavy_bound, huge_q, huge_bound, counters, effective_budget(b_eff, m, k), heavy_state,
+  const NearestScratch ns{heavy_q, heavy_bound, huge_q, huge_bound, counters,
+                          effective_budget(budget, m, k, b->format == ABX_NODES_Q16W), heavy_state,
                           (uint32_t)std::min<int64_t>(state_cap, kMaxSavedHeavy)};
 #define ABX_FMT(KD, FM) nearest_fmt<KD, FM>(b, pts, m, order, k, idx, dist, stats, ns, s)
   if (b->kind == ABX_PRIM_POINTS) ABX_BY_FORMAT(ABX_FMT, ABX_PRIM_POINTS);
