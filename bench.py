@@ -257,8 +257,8 @@ def main():
 
     kernels = ["morton", "sort_onesweep", "sort_hist", "karras", "refit", "refit_mid", "refit_top", "agglo", "agglo_mid",
                "agglo_top", "quantise", "preorder", "wide_flags", "wide_emit",
-               "scene_partial", "query_codes", "spatial_count", "spatial_fill", "scan_tiles", "nearest",
-               "nearest_coop"]
+               "scene_partial", "query_codes", "spatial_count", "spatial_copy", "spatial_fill", "scan_tiles",
+               "nearest", "nearest_coop"]
     ktimes = {}
     for name in kernels:
         ms, cnt = abx.timing_get(name)
@@ -282,9 +282,13 @@ def main():
         "nearest+coop": algorithmic_bytes(st_knn, node_b, leaf_b, 16 + 8 * min(k, n)),
         # query 12 B + order 4 B + count write 4 B
         "spatial_count": algorithmic_bytes(st_sp, node_b, leaf_b, 20),
-        # query 12 B + order 4 B + offsets 8 B, plus 4 B per written index
-        "spatial_fill": algorithmic_bytes(st_sp, node_b, leaf_b, 24) + 4 * hits,
     }
+    # where the first pass kept its rows, the second copies them (and walks for
+    # the few that had no room): one walk in all
+    kept = "spatial_copy" in ktimes
+    if not kept:
+        # query 12 B + order 4 B + offsets 8 B, plus 4 B per written index
+        alg["spatial_fill"] = algorithmic_bytes(st_sp, node_b, leaf_b, 24) + 4 * hits
     dom = max((kn for kn in ktimes if kn not in ("nearest", "nearest_coop")),
               key=lambda kn: ktimes[kn]["ms_per_launch"] * ktimes[kn]["launches_per_step"])
     if dom in alg:
@@ -335,12 +339,12 @@ def main():
     bpp = build_bytes_per_prim(args.nodes, args.morton_bits,
                                depth_first=int(t.layout.node_order) == abx.ORDER_DEPTH_FIRST,
                                wide_per_prim=int(t.layout.node_count) / n if args.nodes == "q16w" else 0.0)
-    rad_bytes = alg["spatial_count"] + alg["spatial_fill"]
+    rad_bytes = alg["spatial_count"] + (4 * hits if kept else alg["spatial_fill"])
     phase_rooflines = {
         "build": dict(bytes_per_prim=bpp, achieved=round(bpp * n / (build_ms * 1e-3) / 1e9, 1),
                       peak=HBM_PEAK_GBS, unit="GB/s",
                       frac=round(bpp * n / (build_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)),
-        "radius_2p": dict(bytes=rad_bytes, achieved=round(rad_bytes / (rad_ms * 1e-3) / 1e9, 1),
+        "radius_2p": dict(walks=1 if kept else 2, bytes=rad_bytes, achieved=round(rad_bytes / (rad_ms * 1e-3) / 1e9, 1),
                           peak=HBM_PEAK_GBS, unit="GB/s",
                           frac=round(rad_bytes / (rad_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)),
     }
