@@ -78,7 +78,7 @@ std::vector<Pending> g_pending;
 std::map<std::string, std::pair<double, int64_t>> g_acc;
 
 constexpr int64_t kMaxCount = INT32_MAX;
-constexpr int64_t kMaxNearestK = 128;  // register lists up to 32, LDS heaps up to 128
+constexpr int64_t kMaxNearestK = 128;  // register lists up to 64, LDS heaps up to 128
 
 __global__ void k_row_offsets(int32_t *off, int64_t m, int32_t k) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -368,7 +368,8 @@ abx_status spatial_finish(const abx_bvh *bvh, const abx_predicates *p, char *sc,
   const int32_t *order =
       what & kScratchOrdered ? reinterpret_cast<const int32_t *>(sc + L.order) : nullptr;
   const int64_t m = p->m;
-  if (!L.keeps || !(what & kScratchKept))
+  // (and where rows turned out long, the few that are whole are not worth the copy)
+  if (!L.keeps || !(what & kScratchKept) || (st.longer && st.total > kKeptExpect * m))
     return launch_spatial(bvh, p->kind, p->data, m, p->radii, p->radius, order, 1 /*fill*/, nullptr,
                           offsets, indices, s);
   const KeptRows kept = kept_rows(sc, L, m);
