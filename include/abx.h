@@ -204,9 +204,10 @@ abx_status abx_bvh_get_layout(const abx_bvh *bvh, abx_bvh_layout *out /*host*/);
  *   returns ABX_OK: from the rows the first traversal kept, if the scratch has
  *   the room that abx_query_spatial_sizes asks for and few hits are expected
  *   (capacity at most 24 a query, and no more by the radius against the density
- *   of primitives in the scene box than there are slots for), else by traversing again (so do rows too long
- *   to keep; a smaller scratch, without that room, is accepted).  Otherwise it returns
- *   ABX_ERR_CAPACITY with offsets and *total valid; the caller may then call
+ *   of primitives in the scene box than there are slots for), else by
+ *   traversing again (so do rows too long to keep; a smaller scratch, without
+ *   that room, is accepted).  The rows are the same either way.  Otherwise it
+ *   returns ABX_ERR_CAPACITY with offsets and *total valid; the caller may then call
  *   abx_query_spatial_fill with a large enough `indices` and the same
  *   scratch (which keeps the query order and rows).  total >= 2^31 gives
  *   ABX_ERR_OVERFLOW.  The user-side estimate `capacity` plays the role of
